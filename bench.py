@@ -84,7 +84,7 @@ def iteration_bytes_per_voxel(precision, L, ordering, precond, nmls):
 
 
 KERNEL_SYMBOL = {"grad": "k_grad", "mls": "k_mls", "dir": "k_dir", "precond_a": None, "precond_b": None,
-                 "resident": "k_resident"}
+                 "resident": "k_resident", "dots": "k_nat_unpack"}
 
 
 def kernel_symbol(kclass, ordering, precond, nz):

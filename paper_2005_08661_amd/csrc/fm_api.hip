@@ -84,7 +84,8 @@ struct fm_plan {
   fm::State *S = nullptr;      // two ping-pong state copies
   double *part = nullptr;      // two ping-pong partial-sum buffers [part_rows][kMaxK]
   size_t part_rows = kMaxGrid;
-  fm::Wavefront wf{};          // natural-order sweep: tiles, tickets, progress
+  fm::Wavefront wf{};          // natural-order sweep: tiles, tickets, packed arrays, face buffers
+  int wf_pack_grid = 1, wf_unpack_grid = 1;
   double *setup_part = nullptr;
   double *nmask = nullptr;
   int32_t *status = nullptr;
@@ -354,6 +355,48 @@ fm_status enqueue_ict(fm_plan *p, const T *g, hipStream_t s, Recorder *rec) {
   return FM_OK;
 }
 
+// Natural-order IC(0): pack, the two sweeps (outside the state chain), unpack
+// with the dot products.  ain and aout are the chain arguments of the first
+// and the last of the four.
+template <typename T>
+fm_status enqueue_natural(fm_plan *p, const fm::IterArgs<T> &ain, const fm::IterArgs<T> &aout, const T *gsrc,
+                          int32_t *status, hipStream_t s, Recorder *rec) {
+  const fm::Wavefront &w = p->wf;
+  FM_LAUNCH(FM_K_DOTS, fm::k_nat_pack<T>, dim3(p->wf_pack_grid), dim3(fm::kNT), s, ain, w, gsrc);
+  FM_LAUNCH_CHECK();
+  FM_LAUNCH(FM_K_PRECOND_A, fm::k_ic_fwd_wave<T>, dim3(w.ntiles), dim3(64), s, w, ain.beta, status);
+  FM_LAUNCH_CHECK();
+  FM_LAUNCH(FM_K_PRECOND_B, fm::k_ic_bwd_wave<T>, dim3(w.ntiles), dim3(64), s, w, ain.beta, status);
+  FM_LAUNCH_CHECK();
+  FM_LAUNCH(FM_K_DOTS, fm::k_nat_unpack<T>, dim3(p->wf_unpack_grid), dim3(fm::kNT), s, aout, w, gsrc);
+  FM_LAUNCH_CHECK();
+  return FM_OK;
+}
+
+// Block red-black IC(0): pack, forward colours 0 and 1, backward colours 1 and
+// 0 (a volume of one tile has no colour-1 tile), unpack.
+template <typename T>
+fm_status enqueue_block(fm_plan *p, const fm::IterArgs<T> &ain, const fm::IterArgs<T> &aout, const T *gsrc, hipStream_t s,
+                        Recorder *rec) {
+  fm::Wavefront w = p->wf;
+  w.ff = nullptr;  // no values pass between tiles of one launch
+  FM_LAUNCH(FM_K_DOTS, fm::k_nat_pack<T>, dim3(p->wf_pack_grid), dim3(fm::kNT), s, ain, w, gsrc);
+  FM_LAUNCH_CHECK();
+  FM_LAUNCH(FM_K_PRECOND_A, (fm::k_icb_fwd<T, false>), dim3(w.nblk[0]), dim3(64), s, w, ain.beta, p->status, 0);
+  FM_LAUNCH_CHECK();
+  if (w.nblk[1] > 0) {
+    FM_LAUNCH(FM_K_PRECOND_A, (fm::k_icb_fwd<T, true>), dim3(w.nblk[1]), dim3(64), s, w, ain.beta, p->status, 1);
+    FM_LAUNCH_CHECK();
+    FM_LAUNCH(FM_K_PRECOND_B, (fm::k_icb_bwd<T, false>), dim3(w.nblk[1]), dim3(64), s, w, ain.beta, 1);
+    FM_LAUNCH_CHECK();
+  }
+  FM_LAUNCH(FM_K_PRECOND_B, (fm::k_icb_bwd<T, true>), dim3(w.nblk[0]), dim3(64), s, w, ain.beta, 0);
+  FM_LAUNCH_CHECK();
+  FM_LAUNCH(FM_K_DOTS, fm::k_nat_unpack<T>, dim3(p->wf_unpack_grid), dim3(fm::kNT), s, aout, w, gsrc);
+  FM_LAUNCH_CHECK();
+  return FM_OK;
+}
+
 template <typename T>
 fm_status enqueue_precond(fm_plan *p, const T *gsrc, hipStream_t s, Recorder *rec = nullptr) {
   auto pargs = [&](fm_plan *pp, uint64_t q) {
@@ -385,30 +428,18 @@ fm_status enqueue_precond(fm_plan *p, const T *gsrc, hipStream_t s, Recorder *re
     FM_LAUNCH_CHECK();
     set_parts(p, 0, 0);
   } else if (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_BLOCKRB) {
-    // block red-black: forward colour 0, colour 1; backward colour 1, colour 0 (a volume of one
-    // tile column and row has no colour-1 tile)
-    const fm::Wavefront &w = p->wf;
-    FM_LAUNCH(FM_K_PRECOND_A, fm::k_icb_fwd<T>, dim3(w.nblk[0]), dim3(64), s, pargs(p, p->q++), w, gsrc, 0);
-    FM_LAUNCH_CHECK();
+    const fm::IterArgs<T> ain = pargs(p, p->q++);
     set_parts(p, 0, 0);
-    if (w.nblk[1] > 0) {
-      FM_LAUNCH(FM_K_PRECOND_A, fm::k_icb_fwd<T>, dim3(w.nblk[1]), dim3(64), s, pargs(p, p->q++), w, gsrc, 1);
-      FM_LAUNCH_CHECK();
-      FM_LAUNCH(FM_K_PRECOND_B, fm::k_icb_bwd<T>, dim3(w.nblk[1]), dim3(64), s, pargs(p, p->q++), w, gsrc, 1);
-      FM_LAUNCH_CHECK();
-      set_parts(p, w.nblk[1], 2);
-    }
-    FM_LAUNCH(FM_K_PRECOND_B, fm::k_icb_bwd<T>, dim3(w.nblk[0]), dim3(64), s, pargs(p, p->q++), w, gsrc, 0);
-    FM_LAUNCH_CHECK();
-    set_parts(p, w.nblk[0], 2);
+    fm_status st = enqueue_block<T>(p, ain, pargs(p, p->q++), gsrc, s, rec);
+    if (st) return st;
+    set_parts(p, p->wf_unpack_grid, 2);
   } else if (p->prm.precond == FM_PRECOND_IC0) {
     if (p->prm.ordering == FM_ORDER_NATURAL) {
-      FM_LAUNCH(FM_K_PRECOND_A, fm::k_ic_fwd_wave<T>, dim3(p->wf.ntiles), dim3(64), s, pargs(p, p->q++), p->wf, gsrc);
-      FM_LAUNCH_CHECK();
+      const fm::IterArgs<T> ain = pargs(p, p->q++);
       set_parts(p, 0, 0);
-      FM_LAUNCH(FM_K_PRECOND_B, fm::k_ic_bwd_wave<T>, dim3(p->wf.ntiles), dim3(64), s, pargs(p, p->q++), p->wf, gsrc);
-      FM_LAUNCH_CHECK();
-      set_parts(p, p->wf.ntiles, 2);
+      fm_status st = enqueue_natural<T>(p, ain, pargs(p, p->q++), gsrc, p->status, s, rec);
+      if (st) return st;
+      set_parts(p, p->wf_unpack_grid, 2);
     } else {
       FM_LAUNCH(FM_K_PRECOND_A, (fm::k_rb_black<T, false>), dim3(p->sgrid), dim3(fm::kNT), s, pargs(p, p->q++), gsrc);
       FM_LAUNCH_CHECK();
@@ -437,7 +468,7 @@ uint64_t launches_per_iteration(const fm_plan *p) {
   uint64_t precond_dir = 2;
   if (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_NATURAL) precond_dir = 3;
   if (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_COLOR3) precond_dir = 5;
-  if (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_BLOCKRB) precond_dir = p->wf.nblk[1] > 0 ? 5 : 3;
+  if (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_BLOCKRB) precond_dir = 3;
   return 1 + precond_dir + (uint64_t)(p->prm.nmls - 1);
 }
 
@@ -713,6 +744,29 @@ fm_status upload_pairs(fm_plan *p, const std::vector<std::complex<double>> &G, v
   return FM_OK;
 }
 
+// IC(0) swept tile by tile (natural and block red-black order).
+bool sweeps_in_tiles(const fm_plan *p) {
+  return p->prm.precond == FM_PRECOND_IC0 && (p->prm.ordering == FM_ORDER_NATURAL || p->prm.ordering == FM_ORDER_BLOCKRB);
+}
+
+// Face buffers and tickets of the natural-order sweeps: rows past a sweep and
+// the last tile (no neighbour) stay 0.
+fm_status alloc_faces(fm_plan *p) {
+  fm::Wavefront &w = p->wf;
+  w.frow = w.nrow + fm::kNatU + fm::kTile - 1;
+  const size_t faces = ((size_t)w.ntiles + 1) * w.frow * fm::kFaceSlots;
+  void *ff = nullptr, *fp = nullptr, *tk = nullptr;
+  if (!plan_alloc(p, &ff, sizeof(fm::Rec) * faces) || !plan_alloc(p, &fp, p->tsize * faces) ||
+      !plan_alloc(p, &tk, sizeof(uint32_t) * 2))
+    return fail(FM_ERR_ALLOC, "hipMalloc of the face buffers failed");
+  if (hipMemset(ff, 0, sizeof(fm::Rec) * faces) != hipSuccess || hipMemset(fp, 0, p->tsize * faces) != hipSuccess)
+    return fail(FM_ERR_HIP, "hipMemset of the face buffers failed");
+  w.ff = (fm::Rec *)ff;
+  w.fp = fp;
+  w.ticket = (uint32_t *)tk;
+  return FM_OK;
+}
+
 fm_status wf_init(fm_plan *p, double *f0, hipStream_t s);  // fm_waterfat.inc
 
 void free_plan(fm_plan *p) {
@@ -942,6 +996,10 @@ fm_status adj_alloc(fm_plan *p) {
   if (hipMemset(p->a_part, 0, sizeof(double) * 2 * p->part_rows * kMaxK) != hipSuccess ||
       hipMemset(p->aS, 0, sizeof(fm::State) * 2) != hipSuccess)
     return fail(FM_ERR_HIP, "hipMemset of the adjoint state failed");
+  if (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_BLOCKRB && !p->wf.ff) {
+    fm_status fs = alloc_faces(p);  // its CG is preconditioned in natural order
+    if (fs) return fs;
+  }
   p->adj_ready = true;
   return FM_OK;
 }
@@ -1024,13 +1082,10 @@ fm_status adj_enqueue_iteration(fm_plan *p, uint64_t &q, int &np, int &nv, int k
   } else if (p->prm.precond == FM_PRECOND_IC0) {
     // natural-order IC(0) also for block red-black plans (v does not depend on the preconditioner)
     if (p->prm.ordering == FM_ORDER_NATURAL || p->prm.ordering == FM_ORDER_BLOCKRB) {
-      FM_LAUNCH(0, fm::k_ic_fwd_wave<T>, dim3(p->wf.ntiles), dim3(64), s, adj_precond_args<T>(p, q++, np, nv), p->wf, r);
-      FM_LAUNCH_CHECK();
-      np = 0;
-      nv = 0;
-      FM_LAUNCH(0, fm::k_ic_bwd_wave<T>, dim3(p->wf.ntiles), dim3(64), s, adj_precond_args<T>(p, q++, np, nv), p->wf, r);
-      FM_LAUNCH_CHECK();
-      np = p->wf.ntiles;
+      const fm::IterArgs<T> ain = adj_precond_args<T>(p, q++, np, nv);
+      fm_status e = enqueue_natural<T>(p, ain, adj_precond_args<T>(p, q++, 0, 0), r, p->a_status, s, rec);
+      if (e) return e;
+      np = p->wf_unpack_grid;
       nv = 2;
     } else {
       FM_LAUNCH(0, (fm::k_rb_black<T, false>), dim3(p->sgrid), dim3(fm::kNT), s, adj_precond_args<T>(p, q++, np, nv), r);
@@ -1221,7 +1276,7 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
   } else {
     for (int i = 0; i < 2; ++i) FM_ALLOC_PAD(p->G[i], ts);
     FM_ALLOC_PAD(p->D, ts);
-    FM_ALLOC_PAD(p->X, ts);
+    if (!sweeps_in_tiles(p)) FM_ALLOC_PAD(p->X, ts);
     FM_ALLOC_PAD(p->P, ts);
     FM_ALLOC_PAD(p->ipiv, sizeof(double));
   }
@@ -1240,11 +1295,9 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
         const int tj = d - ti;
         if (tj >= 0 && tj < w.nty) order.push_back(make_int2(ti, tj));
       }
-    void *ord = nullptr, *cnt = nullptr;
+    void *ord = nullptr;
     FM_ALLOC(ord, sizeof(int2) * order.size());
-    FM_ALLOC(cnt, sizeof(uint32_t) * 2 + sizeof(int32_t) * 2 * (size_t)w.ntiles);
-    if (hipMemcpy(ord, order.data(), sizeof(int2) * order.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemset(cnt, 0, sizeof(uint32_t) * 2 + sizeof(int32_t) * 2 * (size_t)w.ntiles) != hipSuccess)
+    if (hipMemcpy(ord, order.data(), sizeof(int2) * order.size(), hipMemcpyHostToDevice) != hipSuccess)
       return cleanup(fail(FM_ERR_HIP, "wavefront tables upload failed"));
     w.order = (const int2 *)ord;
     // block red-black: the tiles of each colour (ti + tj) mod 2
@@ -1261,10 +1314,28 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
         return cleanup(fail(FM_ERR_HIP, "block tables upload failed"));
       w.blk[c] = (const int2 *)bp;
     }
-    w.ticket_fwd = (uint32_t *)cnt;
-    w.ticket_bwd = (uint32_t *)cnt + 1;
-    w.prog_fwd = (int32_t *)((uint32_t *)cnt + 2);
-    w.prog_bwd = w.prog_fwd + w.ntiles;
+    if (sweeps_in_tiles(p)) {
+      // packed arrays of the natural and block red-black sweeps; the face buffers are the natural
+      // order's (a block red-black plan gets them with the adjoint's workspace)
+      const int U = fm::kNatU;
+      w.nrow = (prm->nz + 2 * (fm::kTile - 1) + 1 + 2 * U - 1) / (2 * U) * (2 * U);
+      w.trow = w.nrow + fm::kTile;
+      const size_t guard = (size_t)(U + fm::kTile) * 64;  // rows read past either end
+      const size_t packed = ((size_t)w.ntiles + 1) * w.trow * 64 + 2 * guard;
+      FM_ALLOC(w.rec, sizeof(fm::Rec) * packed);
+      FM_ALLOC(w.p, ts * packed);
+      if (hipMemset(w.rec, 0, sizeof(fm::Rec) * packed) != hipSuccess || hipMemset(w.p, 0, ts * packed) != hipSuccess)
+        return cleanup(fail(FM_ERR_HIP, "hipMemset of the sweep arrays failed"));
+      w.rec += guard;
+      w.p = (char *)w.p + ts * guard;
+      const int64_t units = (int64_t)w.ntiles * w.nrow, wpb = fm::kNT / fm::kWave;
+      p->wf_pack_grid = (int)std::min<int64_t>(8 * kMaxGrid, (units + wpb - 1) / wpb);
+      p->wf_unpack_grid = (int)std::min<int64_t>(kMaxGrid, (int64_t)w.ntiles * ((prm->nz + fm::kUnpackZ - 1) / fm::kUnpackZ));
+      if (prm->ordering == FM_ORDER_NATURAL) {
+        fm_status fs = alloc_faces(p);
+        if (fs) return cleanup(fs);
+      }
+    }
     p->part_rows = (size_t)(w.ntiles > kMaxGrid ? w.ntiles : kMaxGrid);
   }
   FM_ALLOC(p->part, sizeof(double) * 2 * p->part_rows * kMaxK);
