@@ -23,6 +23,7 @@
 #include "fm_resident.hpp"
 #include "fm_order2.hpp"
 #include "fm_ict.hpp"
+#include "fm_ict_tile.hpp"
 #include "fm_tile.hpp"
 
 using fm::kBlock;
@@ -134,6 +135,9 @@ struct fm_plan {
   int ict_noff = 0, ict_nlev = 0, ict_kcol = 0, ict_blocks = 0;
   double *ict_lo = nullptr, *ict_ld = nullptr, *ict_y = nullptr, *ict_pd = nullptr;
   double *ict_hmax = nullptr, *ict_hpart = nullptr;
+  bool ict_tiled = false;      // fill levels 0 and 1: one launch per sweep
+  fm::IctSweep ict_sweep{};
+  int ict_pack_grid = 1, ict_unpack_grid = 1;
 };
 
 namespace {
@@ -322,10 +326,39 @@ void set_parts(fm_plan *p, int nparts, int nvals) {
   p->last_nvals = nvals;
 }
 
-// IC_t: H_max, then the factorisation with the forward solve level by level,
-// then the backward solve in reverse level order (outside the state chain).
+// IC_t: H_max, the factorisation with the forward solve, and the backward solve
+// (outside the state chain), then the dot products.
+template <typename T>
+fm_status enqueue_ict_hmax(fm_plan *p, hipStream_t s, Recorder *rec) {
+  FM_LAUNCH(FM_K_PRECOND_A, fm::k_ict_hmax<T>, dim3(p->grid), dim3(kBlock), s, p->geo, (const uint8_t *)p->code,
+            (const T *)p->D, p->prm.beta, p->ict_hpart);
+  FM_LAUNCH_CHECK();
+  FM_LAUNCH(FM_K_PRECOND_A, fm::k_ict_hmax_fin, dim3(1), dim3(kBlock), s, (const double *)p->ict_hpart, p->grid,
+            p->ict_hmax);
+  FM_LAUNCH_CHECK();
+  return FM_OK;
+}
+
+// Fill levels 0 and 1: one launch per sweep.
 template <typename T, int LEVEL>
-fm_status enqueue_ict(fm_plan *p, const T *g, hipStream_t s, Recorder *rec) {
+fm_status enqueue_ict_tiled(fm_plan *p, const T *g, const fm::IterArgs<T> &a, const T *gsrc, hipStream_t s, Recorder *rec) {
+  const fm::IctSweep &w = p->ict_sweep;
+  FM_LAUNCH(FM_K_PRECOND_A, (fm::k_ict_pack<T, LEVEL>), dim3(p->ict_pack_grid), dim3(fm::kNT), s, p->geo, p->prm.beta,
+            p->prm.ict_factor, (const double *)p->ict_hmax, (const uint8_t *)p->code, (const T *)p->D, g, w);
+  FM_LAUNCH_CHECK();
+  FM_LAUNCH(FM_K_PRECOND_A, (fm::k_ict_fwd_wave<LEVEL>), dim3(w.ntiles), dim3(64), s, w, p->status);
+  FM_LAUNCH_CHECK();
+  FM_LAUNCH(FM_K_PRECOND_B, (fm::k_ict_bwd_wave<LEVEL>), dim3(w.ntiles), dim3(64), s, w, p->status);
+  FM_LAUNCH_CHECK();
+  FM_LAUNCH(FM_K_DOTS, (fm::k_ict_unpack<T, LEVEL>), dim3(p->ict_unpack_grid), dim3(fm::kNT), s, a, w, gsrc);
+  FM_LAUNCH_CHECK();
+  return FM_OK;
+}
+
+// Fill level 2: a launch per level of the schedule.
+template <typename T>
+fm_status enqueue_ict_levels(fm_plan *p, const T *g, hipStream_t s, Recorder *rec) {
+  constexpr int LEVEL = 2;
   fm::IctArgs<T> a{};
   a.geo = p->geo;
   a.beta = p->prm.beta;
@@ -340,12 +373,6 @@ fm_status enqueue_ict(fm_plan *p, const T *g, hipStream_t s, Recorder *rec) {
   a.pd = p->ict_pd;
   a.P = (T *)p->P;
   a.status = p->status;
-  FM_LAUNCH(FM_K_PRECOND_A, fm::k_ict_hmax<T>, dim3(p->grid), dim3(kBlock), s, p->geo, (const uint8_t *)p->code,
-            (const T *)p->D, p->prm.beta, p->ict_hpart);
-  FM_LAUNCH_CHECK();
-  FM_LAUNCH(FM_K_PRECOND_A, fm::k_ict_hmax_fin, dim3(1), dim3(kBlock), s, (const double *)p->ict_hpart, p->grid,
-            p->ict_hmax);
-  FM_LAUNCH_CHECK();
   for (int lv = 0; lv < p->ict_nlev; ++lv)
     FM_LAUNCH(FM_K_PRECOND_A, (fm::k_ict_fwd<T, LEVEL>), dim3(p->ict_blocks), dim3(fm::kIctNT), s, a, g, lv);
   FM_LAUNCH_CHECK();
@@ -406,8 +433,17 @@ fm_status enqueue_precond(fm_plan *p, const T *gsrc, hipStream_t s, Recorder *re
   };
   if (p->prm.precond == FM_PRECOND_ICT) {
     const T *g = gsrc ? gsrc : (const T *)p->G[p->iter_host & 1];
-    fm_status st = p->prm.ict_level == 0 ? enqueue_ict<T, 0>(p, g, s, rec)
-                   : (p->prm.ict_level == 1 ? enqueue_ict<T, 1>(p, g, s, rec) : enqueue_ict<T, 2>(p, g, s, rec));
+    fm_status st = enqueue_ict_hmax<T>(p, s, rec);
+    if (st) return st;
+    if (p->ict_tiled) {
+      const fm::IterArgs<T> a = pargs(p, p->q++);
+      st = p->prm.ict_level == 0 ? enqueue_ict_tiled<T, 0>(p, g, a, gsrc, s, rec)
+                                 : enqueue_ict_tiled<T, 1>(p, g, a, gsrc, s, rec);
+      if (st) return st;
+      set_parts(p, p->ict_unpack_grid, 2);
+      return FM_OK;
+    }
+    st = enqueue_ict_levels<T>(p, g, s, rec);
     if (st) return st;
     FM_LAUNCH(FM_K_DOTS, fm::k_ict_dots<T>, dim3(p->sgrid), dim3(fm::kNT), s, pargs(p, p->q++),
               (const double *)p->ict_pd, gsrc);
@@ -767,6 +803,48 @@ fm_status alloc_faces(fm_plan *p) {
   return FM_OK;
 }
 
+// Tables and arrays of the tiled IC_t sweeps (fm_ict_tile.hpp).
+template <int LEVEL>
+fm_status alloc_ict_sweep(fm_plan *p) {
+  using C = fm::IctTile<LEVEL>;
+  fm::IctSweep &w = p->ict_sweep;
+  const int U = fm::kIctU, t = fm::kTile;
+  w.ntx = (p->geo.nx + t - 1) / t;
+  w.nty = (p->geo.ny + 7 * C::K + t - 1) / t;
+  w.ntiles = w.ntx * w.nty;
+  w.nrow = (p->geo.nz + C::skew + 2 * U - 1) / (2 * U) * (2 * U);
+  w.frow = w.nrow + 8 * (C::K + 1) + 8 + U;
+  std::vector<int2> order;
+  order.reserve((size_t)w.ntiles);
+  for (int i = 0; i < w.ntx; ++i)
+    for (int c = 0; c < w.nty; ++c) order.push_back(make_int2(i, c));
+  auto first = [](int2 v) { return v.x + (int64_t)(C::K + 1) * (C::K * v.x + v.y); };  // its first step / 8
+  std::stable_sort(order.begin(), order.end(), [&](int2 a, int2 b) { return first(a) < first(b); });
+  const size_t row = (size_t)C::planes * 64, packed = ((size_t)w.ntiles * w.nrow + 2 * U) * row;
+  const size_t faces = ((size_t)w.ntiles + 1) * w.frow * fm::kFaceSlots;
+  void *ord = nullptr, *tk = nullptr, *rec = nullptr, *ff = nullptr, *fb = nullptr;
+  if (!plan_alloc(p, &ord, sizeof(int2) * order.size()) || !plan_alloc(p, &tk, sizeof(uint32_t) * 2) ||
+      !plan_alloc(p, &rec, sizeof(fm::Rec) * packed) || !plan_alloc(p, &ff, sizeof(fm::Rec) * faces * C::fr) ||
+      !plan_alloc(p, &fb, sizeof(fm::Rec) * faces * C::br))
+    return fail(FM_ERR_ALLOC, "hipMalloc of the IC_t sweep arrays failed");
+  if (hipMemcpy(ord, order.data(), sizeof(int2) * order.size(), hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemset(rec, 0, sizeof(fm::Rec) * packed) != hipSuccess)
+    return fail(FM_ERR_HIP, "set-up of the IC_t sweep arrays failed");
+  w.order = (const int2 *)ord;
+  w.ticket = (uint32_t *)tk;
+  w.rec = (fm::Rec *)rec + U * row;
+  w.ff = (fm::Rec *)ff;
+  w.fb = (fm::Rec *)fb;
+  hipLaunchKernelGGL(fm::k_ict_faces<LEVEL>, dim3(kMaxGrid), dim3(kBlock), 0, nullptr, w);
+  FM_LAUNCH_CHECK();
+  FM_HIP(hipStreamSynchronize(nullptr));
+  const int64_t units = (int64_t)w.ntiles * w.nrow, wpb = fm::kNT / fm::kWave;
+  p->ict_pack_grid = (int)std::min<int64_t>(8 * kMaxGrid, (units + wpb - 1) / wpb);
+  p->ict_unpack_grid = (int)std::min<int64_t>(kMaxGrid, (int64_t)w.ntiles * ((p->geo.nz + fm::kUnpackZ - 1) / fm::kUnpackZ));
+  p->ict_tiled = true;
+  return FM_OK;
+}
+
 fm_status wf_init(fm_plan *p, double *f0, hipStream_t s);  // fm_waterfat.inc
 
 void free_plan(fm_plan *p) {
@@ -907,8 +985,8 @@ fm_status run_graph(fm_plan *p, int niter, hipStream_t s);
 fm_status run_iterations(fm_plan *p, int niter, hipStream_t s) {
   if (niter <= 0) return FM_OK;
   if (use_resident(p)) return run_resident(p, niter, s);
-  if (!p->ict) return run_graph(p, niter, s);
-  // IC_t launches a kernel per wavefront level (thousands per iteration): one
+  if (!p->ict || p->ict_tiled) return run_graph(p, niter, s);
+  // IC_t of fill level 2 launches a kernel per wavefront level (thousands per iteration): one
   // graph of one iteration, replayed niter times
   for (int i = 0; i < niter; ++i) {
     fm_status st = run_graph(p, 1, s);
@@ -1360,18 +1438,23 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
     }
     p->ict = true;
     p->ict_noff = noff;
-    p->ict_nlev = wa * (prm->nx - 1) + wb * (prm->ny - 1) + (prm->nz - 1) + 1;
-    p->ict_kcol = (prm->nz - 1) / wb + 1;
-    p->ict_blocks = (int)(((int64_t)prm->nx * p->ict_kcol + fm::kIctNT - 1) / fm::kIctNT);
-    FM_ALLOC(p->ict_lo, sizeof(double) * n * (size_t)noff);
-    FM_ALLOC(p->ict_ld, sizeof(double) * n);
-    FM_ALLOC(p->ict_y, sizeof(double) * n);
-    FM_ALLOC(p->ict_pd, sizeof(double) * n);
     FM_ALLOC(p->ict_hmax, sizeof(double));
     FM_ALLOC(p->ict_hpart, sizeof(double) * kMaxGrid);
-    if (hipMemset(p->ict_lo, 0, sizeof(double) * n * (size_t)noff) != hipSuccess ||
-        hipMemset(p->ict_ld, 0, sizeof(double) * n) != hipSuccess)
-      return cleanup(fail(FM_ERR_HIP, "hipMemset of the IC_t factor failed"));
+    if (prm->ict_level < 2) {
+      fm_status is = prm->ict_level == 0 ? alloc_ict_sweep<0>(p) : alloc_ict_sweep<1>(p);
+      if (is) return cleanup(is);
+    } else {
+      p->ict_nlev = wa * (prm->nx - 1) + wb * (prm->ny - 1) + (prm->nz - 1) + 1;
+      p->ict_kcol = (prm->nz - 1) / wb + 1;
+      p->ict_blocks = (int)(((int64_t)prm->nx * p->ict_kcol + fm::kIctNT - 1) / fm::kIctNT);
+      FM_ALLOC(p->ict_lo, sizeof(double) * n * (size_t)noff);
+      FM_ALLOC(p->ict_ld, sizeof(double) * n);
+      FM_ALLOC(p->ict_y, sizeof(double) * n);
+      FM_ALLOC(p->ict_pd, sizeof(double) * n);
+      if (hipMemset(p->ict_lo, 0, sizeof(double) * n * (size_t)noff) != hipSuccess ||
+          hipMemset(p->ict_ld, 0, sizeof(double) * n) != hipSuccess)
+        return cleanup(fail(FM_ERR_HIP, "hipMemset of the IC_t factor failed"));
+    }
   }
   if (prm->model == FM_WATERFAT) {
     FM_ALLOC(p->rho, sizeof(double) * n);
@@ -1443,6 +1526,16 @@ fm_status fm_get_factor(fm_plan *p, double *L, hipStream_t s) {
   if (!L) return fail(FM_ERR_ARG, "L must not be NULL");
   if (!p->ict) return fail(FM_ERR_ARG, "the plan's preconditioner is not IC_t");
   const size_t n = (size_t)p->n;
+  if (p->ict_tiled) {
+    if (p->prm.ict_level == 0)
+      hipLaunchKernelGGL(fm::k_ict_factor<0>, dim3(p->grid), dim3(kBlock), 0, s, p->geo, (const uint8_t *)p->code,
+                         p->ict_sweep, L, (double *)nullptr);
+    else
+      hipLaunchKernelGGL(fm::k_ict_factor<1>, dim3(p->grid), dim3(kBlock), 0, s, p->geo, (const uint8_t *)p->code,
+                         p->ict_sweep, L, (double *)nullptr);
+    FM_LAUNCH_CHECK();
+    return FM_OK;
+  }
   FM_HIP(hipMemcpyAsync(L, p->ict_ld, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
   FM_HIP(hipMemcpyAsync(L + n, p->ict_lo, sizeof(double) * n * (size_t)p->ict_noff, hipMemcpyDeviceToDevice, s));
   return FM_OK;
@@ -1575,7 +1668,15 @@ fm_status fm_precondition(fm_plan *p, const double *curv, const double *g, doubl
     } else {
       hipLaunchKernelGGL(fm::k_from_work<T>, dim3(p->grid), dim3(kBlock), 0, s, p->n, (const T *)p->P, pout);
       FM_LAUNCH_CHECK();
-      if (piv && p->ict) {
+      if (piv && p->ict_tiled) {
+        if (p->prm.ict_level == 0)
+          hipLaunchKernelGGL(fm::k_ict_factor<0>, dim3(p->grid), dim3(kBlock), 0, s, p->geo, (const uint8_t *)p->code,
+                             p->ict_sweep, (double *)nullptr, piv);
+        else
+          hipLaunchKernelGGL(fm::k_ict_factor<1>, dim3(p->grid), dim3(kBlock), 0, s, p->geo, (const uint8_t *)p->code,
+                             p->ict_sweep, (double *)nullptr, piv);
+        FM_LAUNCH_CHECK();
+      } else if (piv && p->ict) {
         hipLaunchKernelGGL(fm::k_ict_piv, dim3(p->grid), dim3(kBlock), 0, s, p->n, (const uint8_t *)p->code,
                            (const double *)p->ict_ld, piv);
         FM_LAUNCH_CHECK();

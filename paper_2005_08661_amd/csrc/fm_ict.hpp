@@ -9,7 +9,8 @@
 // largest magnitude in H), and L_jj = sqrt(H_jj - sum_k L_jk^2).  The solves
 // are L y = g in natural order and L^T p = y in reverse.
 //
-// Schedule: every offset o = (dx, dy, dz) of the pattern satisfies
+// Schedule (fill level 2; levels 0 and 1 run one launch per sweep,
+// fm_ict_tile.hpp): every offset o = (dx, dy, dz) of the pattern satisfies
 // a dx + b dy + dz >= 1 for the level's weights (a, b) (level 0: 1, 1;
 // level 1: 3, 2; level 2: 7, 3), so the voxels with a x + b y + z = s depend
 // only on voxels of smaller s.  One launch handles one such level s (the

@@ -59,3 +59,25 @@ def test_nan_of_any_payload_passes_between_tiles(prec):
         plan.status()
     p = p.cpu().numpy()
     assert np.isnan(p[12, 12, 10]) and np.isnan(p[23, 23, 19]) and np.isnan(p[0, 0, 0])
+
+
+@pytest.mark.parametrize("level", [0, 1])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_ict_factor_and_solve_match_oracle(shape, level):
+    """IC_t in tiles sheared along x: the factor and its drop set as the oracle's (same arithmetic, quotients
+    correctly rounded up to an ulp: 1e-12), p to 1e-11 of its largest value."""
+    for frac in (1.0, 0.6):
+        curv, g, mask = problem(shape, frac, 43)
+        prm = fmap.make_params(shape, 1, [0.0, 2e-3, 5e-3], 0.1, niter=1, precision=fmap.F64, precond=fmap.ICT,
+                               ict_factor=1e-2, ict_level=level)
+        pb = O.Problem(shape, [0.0, 2e-3, 5e-3], O.gamma_fieldmap(3), 0.1, precond=O.ICT, ict_factor=1e-2, ict_level=level)
+        Lref = O.ict_factor(pb, mask, curv)
+        pref = O.ict_apply(pb, mask, Lref, g)
+        with fmap.Plan(prm) as plan:
+            plan.setup(torch.ones((1, 3) + shape, dtype=torch.complex64, device="cuda"), None, torch.from_numpy(mask).cuda())
+            piv, p = (t.cpu().numpy() for t in plan.precondition(torch.from_numpy(curv).cuda(), torch.from_numpy(g).cuda()))
+            L = plan.factor().cpu().numpy()
+        assert np.array_equal(L == 0, Lref == 0)
+        np.testing.assert_allclose(L, Lref, rtol=1e-12, atol=0)
+        np.testing.assert_allclose(piv, Lref[0] ** 2, rtol=1e-12, atol=0)
+        assert np.abs(p - pref).max() <= 1e-11 * np.abs(pref).max()
