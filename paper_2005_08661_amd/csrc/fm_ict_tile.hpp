@@ -29,8 +29,12 @@
 // ones (Markstein, Computation of elementary functions on the IBM RISC System/6000
 // processor, IBM J. Res. Dev. 34, 1990), in 3 operations instead of a division.
 //
-// Measured at 128x128x64 (MIX, level 1): forward 3.0 ms -> 613 us, backward 2.8 ms
-// -> 349 us a sweep, k_ict_pack 20 us and k_ict_unpack 15 us on top.
+// Measured at 128x128x64 (MIX, level 1): forward 3.0 ms -> 500 us, backward 2.8 ms
+// -> 323 us a sweep, k_ict_pack 20 us and k_ict_unpack 15 us on top.  A step takes
+// 0.48 us forward and 0.30 us backward, of which the issue of its nine 16-byte
+// stores is a good part: stored while the next step's LDS reads are under way they
+// cost 613 -> 500 us, and the face values stored ahead of that instead (a shorter
+// hop, a longer step) measured 530 us.
 #pragma once
 
 #include "fm_ict.hpp"
@@ -296,74 +300,104 @@ __global__ __launch_bounds__(64) void k_ict_fwd_wave(IctSweep w, int32_t *status
   double p_l = 1.0, p_r = 1.0, p_y = 0.0, p_t = __builtin_inf(), p_row[NO];
 #pragma unroll
   for (int u = 0; u < NO; ++u) p_row[u] = 0.0;
-  int err = 0;
+  bool bad5 = false, bad6 = false;
+  // Store the previous row, row k - 1 of the views: to the packed rows and, from
+  // the face lanes, to the face buffer.
+  auto store = [&](__amdgpu_buffer_rsrc_t v, __amdgpu_buffer_rsrc_t vo, int k) {
+    double f[2 * C::fr];
+    f[0] = p_l;
+    f[1] = p_r;
+    f[2] = p_y;
+    f[3] = p_t;
+#pragma unroll
+    for (int u = 4; u < 2 * C::fr; ++u) f[u] = 0.0;
+#pragma unroll
+    for (int u = 0; u < NO; ++u)
+      if (ict_shared<LEVEL>(u)) f[ict_field<LEVEL>(u)] = p_row[u];
+#pragma unroll
+    for (int u = 0; u < C::fr; ++u) face_st(vo, (so + k * kFaceSlots) * C::fr + u, rec2(f[2 * u], f[2 * u + 1]));
+    view_st(v, lane + k * C::planes * 64, rec2(p_l, p_r));
+    view_st(v, lane + (k * C::planes + 1) * 64, rec2(p_y, 0.0));
+#pragma unroll
+    for (int u = 0; u < NO; u += 2)
+      view_st(v, lane + (k * C::planes + 2 + u / 2) * 64,
+              rec2(p_row[u], u + 1 < NO ? p_row[u + 1 < NO ? u + 1 : 0] : 0.0));
+  };
   auto compute = [&](const Set &s, int S0) {
-    const auto v = plane_view(rows + (int64_t)S0 * C::planes * 64, U * C::planes * 64 * (uint32_t)sizeof(Rec));
-    const auto vo = plane_view(out + (int64_t)S0 * kFaceSlots * C::fr, U * kFaceSlots * C::fr * (uint32_t)sizeof(Rec));
+    const auto v = plane_view(rows + (int64_t)(S0 - 1) * C::planes * 64, U * C::planes * 64 * (uint32_t)sizeof(Rec));
+    const auto vo = plane_view(out + (int64_t)(S0 - 1) * kFaceSlots * C::fr, U * kFaceSlots * C::fr * (uint32_t)sizeof(Rec));
 #pragma unroll
     for (int k = 0; k < U; ++k) {
       const int S = S0 + k;
       auto at = [&](int u, int f) {
-        return ring[(((S - ict_back<LEVEL>(u)) & (kIctRing - 1)) * NF + f) * kIctPos + pos - IctPattern<LEVEL>::off[u][0] * 9 -
-                    ict_dy<LEVEL>(u)];
+        return ring[(((S - ict_back<LEVEL>(u)) & (kIctRing - 1)) * NF + f) * kIctPos + pos -
+                    IctPattern<LEVEL>::off[u][0] * 9 - ict_dy<LEVEL>(u)];
       };
+      // everything of other lanes' rows is read first, and the previous row
+      // stored while the reads are under way
+      double lkk[NO], rkk[NO], tk[NO], yk[NO], lkm[NO][NO];
+#pragma unroll
+      for (int u = 0; u < NO; ++u) {
+        lkk[u] = ict_own<LEVEL>(u) ? p_l : at(u, 0);
+        rkk[u] = ict_own<LEVEL>(u) ? p_r : at(u, 1);
+        yk[u] = ict_own<LEVEL>(u) ? p_y : at(u, 2);
+        tk[u] = ict_own<LEVEL>(u) ? p_t : at(u, 3);
+#pragma unroll
+        for (int e = 0; e < NO; ++e) {
+          const int m = e < u ? ict_pair<LEVEL>(u, e) : -1;
+          lkm[u][e] = m < 0 ? 0.0 : (ict_own<LEVEL>(u) ? p_row[m < 0 ? 0 : m] : at(u, ict_field<LEVEL>(m < 0 ? 0 : m)));
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (S > 0) store(v, vo, k);
+      __builtin_amdgcn_sched_barrier(0);
       const double h = rec_d(s.h[k]), t = rec_d2(s.h[k]), gj = rec_d(s.g[k]), nbeta = rec_d2(s.g[k]);
-      double row[NO], ny[NO];
+      double row[NO];
 #pragma unroll
       for (int u = 0; u < NO; ++u) {
         double sum = ict_stencil<LEVEL>(u) ? nbeta : 0.0;  // H_jk
 #pragma unroll
-        for (int e = 0; e < u; ++e) {
-          const int m = ict_pair<LEVEL>(u, e);
-          if (m >= 0) sum = sum - row[e] * (ict_own<LEVEL>(u) ? p_row[m >= 0 ? m : 0] : at(u, ict_field<LEVEL>(m >= 0 ? m : 0)));
-        }
-        const double lkk = ict_own<LEVEL>(u) ? p_l : at(u, 0), rkk = ict_own<LEVEL>(u) ? p_r : at(u, 1), tk = ict_own<LEVEL>(u) ? p_t : at(u, 3);
-        ny[u] = ict_own<LEVEL>(u) ? p_y : at(u, 2);
-        const double val = quotient(sum, lkk, rkk);
-        row[u] = fabs(val) < tk ? 0.0 : val;
+        for (int e = 0; e < u; ++e)
+          if (ict_pair<LEVEL>(u, e) >= 0) sum = sum - row[e] * lkm[u][e];
+        const double val = quotient(sum, lkk[u], rkk[u]);
+        row[u] = fabs(val) < tk[u] ? 0.0 : val;
       }
       double diag = h;
 #pragma unroll
       for (int u = 0; u < NO; ++u) diag = diag - row[u] * row[u];
-      const bool bad = !(diag > 0.0);
-      if (bad) err = max(err, isfinite(diag) ? 5 : 6);
-      const double ljj = bad ? 0.0 : sqrt(diag);
-      double q = __builtin_amdgcn_rcp(ljj);  // 1 / L_jj by the Newton steps of a division
-      q = fma(q, fma(-ljj, q, 1.0), q);
-      q = fma(q, fma(-ljj, q, 1.0), q);
-      q = fma(q, fma(-ljj, q, 1.0), q);
-      const double rjj = bad ? 0.0 : q;
+      const bool good = diag > 0.0, fin = fabs(diag) < __builtin_inf();
+      bad5 |= !good && fin;
+      bad6 |= !good && !fin;
+      // L_jj = sqrt(diag) and 1 / L_jj: the steps of a square root without its
+      // scaling, which a normal diag does not need (the same value), and the
+      // reciprocal from the half of 1 / sqrt that they carry
+      const double q = __builtin_amdgcn_rsq(diag);
+      double l = diag * q, r = 0.5 * q;
+      double e = fma(-r, l, 0.5);
+      l = fma(l, e, l);
+      r = fma(r, e, r);
+      l = fma(fma(-l, l, diag), r, l);
+      l = fma(fma(-l, l, diag), r, l);
+      r = 2.0 * r;
+      r = fma(r, fma(-l, r, 1.0), r);
+      r = fma(r, fma(-l, r, 1.0), r);
       double yv = gj;
 #pragma unroll
-      for (int u = 0; u < NO; ++u) yv = yv - row[u] * ny[u];
-      const double yj = quotient(yv, ljj, rjj);
-      double f[2 * C::fr];
-      f[0] = ljj;
-      f[1] = rjj;
-      f[2] = yj;
-      f[3] = t;
-#pragma unroll
-      for (int u = 4; u < 2 * C::fr; ++u) f[u] = 0.0;
-#pragma unroll
-      for (int u = 0; u < NO; ++u)
-        if (ict_shared<LEVEL>(u)) f[ict_field<LEVEL>(u)] = row[u];
-      double *d = ring + (S & (kIctRing - 1)) * NF * kIctPos + pos;
-#pragma unroll
-      for (int u = 0; u < NF; ++u) d[u * kIctPos] = f[u];
-#pragma unroll
-      for (int u = 0; u < C::fr; ++u)
-        face_st(vo, (so + k * kFaceSlots) * C::fr + u, rec2(f[2 * u], f[2 * u + 1]));
-      view_st(v, lane + k * C::planes * 64, rec2(ljj, rjj));
-      view_st(v, lane + (k * C::planes + 1) * 64, rec2(yj, 0.0));
-#pragma unroll
-      for (int u = 0; u < NO; u += 2)
-        view_st(v, lane + (k * C::planes + 2 + u / 2) * 64, rec2(row[u], u + 1 < NO ? row[u + 1 < NO ? u + 1 : 0] : 0.0));
-      p_l = ljj;
-      p_r = rjj;
-      p_y = yj;
+      for (int u = 0; u < NO; ++u) yv = yv - row[u] * yk[u];
+      p_l = good ? l : 0.0;
+      p_r = good ? r : 0.0;
+      p_y = quotient(yv, p_l, p_r);
       p_t = t;
 #pragma unroll
       for (int u = 0; u < NO; ++u) p_row[u] = row[u];
+      double *d = ring + (S & (kIctRing - 1)) * NF * kIctPos + pos;
+      d[0] = p_l;
+      d[kIctPos] = p_r;
+      d[2 * kIctPos] = p_y;
+      d[3 * kIctPos] = p_t;
+#pragma unroll
+      for (int u = 0; u < NO; ++u)
+        if (ict_shared<LEVEL>(u)) d[ict_field<LEVEL>(u) * kIctPos] = row[u];
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the next step reads other lanes' places
     }
   };
@@ -386,7 +420,10 @@ __global__ __launch_bounds__(64) void k_ict_fwd_wave(IctSweep w, int32_t *status
     issue(A, S0 + 2 * U);  // past the end: the guard rows
     compute(B, S0 + U);
   }
-  if (err) set_status(status, err);
+  store(plane_view(rows + (int64_t)(nrow - 1) * C::planes * 64, C::planes * 64 * (uint32_t)sizeof(Rec)),
+        plane_view(out + (int64_t)(nrow - 1) * kFaceSlots * C::fr, kFaceSlots * C::fr * (uint32_t)sizeof(Rec)), 0);
+  if (bad5) set_status(status, 5);
+  if (bad6) set_status(status, 6);
 }
 
 // Backward solve L^T p = y: p_j = (y_j - sum_i L_ij p_i) / L_jj over the later
@@ -467,32 +504,41 @@ __global__ __launch_bounds__(64) void k_ict_bwd_wave(IctSweep w, int32_t *status
       for (int k = 2; k < C::planes; ++k) s.e[u][k - 2] = view_ld(v, lane + ((U - 1 - u) * C::planes + k) * 64, Rec());
     }
   };
-  double own = 0.0;  // this column's product of the previous step
+  // this lane's previous step: its column's product, those for other lanes, y and p
+  double own = 0.0, c[2 * C::br], p_y = 0.0, p = 0.0;
+#pragma unroll
+  for (int u = 0; u < 2 * C::br; ++u) c[u] = 0.0;
+  auto store = [&](__amdgpu_buffer_rsrc_t v, __amdgpu_buffer_rsrc_t vo, int k) {  // step k - 1 of the views
+#pragma unroll
+    for (int u = 0; u < C::br; ++u) face_st(vo, (so + k * kFaceSlots) * C::br + u, rec2(c[2 * u], c[2 * u + 1]));
+    view_st(v, lane + ((U - 1 - k) * C::planes + 1) * 64, rec2(p_y, p));
+  };
   auto compute = [&](const Set &s, int B0) {
-    const auto v = plane_view(rows - (int64_t)B0 * C::planes * 64, U * C::planes * 64 * (uint32_t)sizeof(Rec));
-    const auto vo = plane_view(out + (int64_t)B0 * kFaceSlots * C::br, U * kFaceSlots * C::br * (uint32_t)sizeof(Rec));
+    // views that begin one step earlier (rows run the other way)
+    const auto v = plane_view(rows - (int64_t)(B0 - 1) * C::planes * 64, U * C::planes * 64 * (uint32_t)sizeof(Rec));
+    const auto vo = plane_view(out + (int64_t)(B0 - 1) * kFaceSlots * C::br, U * kFaceSlots * C::br * (uint32_t)sizeof(Rec));
 #pragma unroll
     for (int k = 0; k < U; ++k) {
       const int S = B0 + k;
-      double sum = rec_d(s.y[k]) - own;
+      double o[NF];
 #pragma unroll
-      for (int u = NO - 2; u >= 0; --u)
-        sum = sum - ring[(((S - ict_back<LEVEL>(u)) & (kIctRing - 1)) * NF + u) * kIctPos + pos + IctPattern<LEVEL>::off[u][0] * 9 +
-                         ict_dy<LEVEL>(u)];
-      const double p = quotient(sum, rec_d(s.l[k]), rec_d2(s.l[k]));
-      double c[2 * C::br];
+      for (int u = 0; u < NF; ++u)
+        o[u] = ring[(((S - ict_back<LEVEL>(u)) & (kIctRing - 1)) * NF + u) * kIctPos + pos +
+                    IctPattern<LEVEL>::off[u][0] * 9 + ict_dy<LEVEL>(u)];
+      __builtin_amdgcn_sched_barrier(0);
+      if (S > 0) store(v, vo, k);
+      __builtin_amdgcn_sched_barrier(0);
+      p_y = rec_d(s.y[k]);
+      double sum = p_y - own;
 #pragma unroll
-      for (int u = 0; u < 2 * C::br; ++u) c[u] = 0.0;
+      for (int u = NF - 1; u >= 0; --u) sum = sum - o[u];
+      p = quotient(sum, rec_d(s.l[k]), rec_d2(s.l[k]));
 #pragma unroll
       for (int u = 0; u < NF; ++u) c[u] = (u & 1 ? rec_d2(s.e[k][u / 2]) : rec_d(s.e[k][u / 2])) * p;
-      own = ((NO - 1) & 1 ? rec_d2(s.e[k][(NO - 1) / 2]) : rec_d(s.e[k][(NO - 1) / 2])) * p;
+      own = (NF & 1 ? rec_d2(s.e[k][NF / 2]) : rec_d(s.e[k][NF / 2])) * p;
       double *d = ring + (S & (kIctRing - 1)) * NF * kIctPos + pos;
 #pragma unroll
       for (int u = 0; u < NF; ++u) d[u * kIctPos] = c[u];
-#pragma unroll
-      for (int u = 0; u < C::br; ++u)
-        face_st(vo, (so + k * kFaceSlots) * C::br + u, rec2(c[2 * u], c[2 * u + 1]));
-      view_st(v, lane + ((U - 1 - k) * C::planes + 1) * 64, rec2(rec_d(s.y[k]), p));
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
   };
@@ -515,6 +561,9 @@ __global__ __launch_bounds__(64) void k_ict_bwd_wave(IctSweep w, int32_t *status
     issue(A, B0 + 2 * U);
     compute(B, B0 + U);
   }
+  // (k = 0 of a view is the row before it: here the first row, the last step's)
+  store(plane_view(rows - (int64_t)(nrow - 1) * C::planes * 64, U * C::planes * 64 * (uint32_t)sizeof(Rec)),
+        plane_view(out + (int64_t)(nrow - 1) * kFaceSlots * C::br, kFaceSlots * C::br * (uint32_t)sizeof(Rec)), 0);
 }
 
 // The packed place of a voxel.
