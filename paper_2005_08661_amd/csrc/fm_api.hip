@@ -98,6 +98,7 @@ struct fm_plan {
   double *gabs = nullptr;
   double *rho = nullptr;
   double *f0buf = nullptr;
+  double2 *sweep_rot = nullptr;  // water-fat sweep: rotation of each pair between sweep values
   double *wf_tmp = nullptr;  // water-fat init: swept map and 3 CG vectors
   bool setup_done = false;
   bool solved = false;
@@ -216,8 +217,16 @@ template <typename T>
 using SetupKernel = void (*)(fm::SetupArgs<T>);
 template <typename T>
 SetupKernel<T> setup_kernel(int lmax, bool wf, int necho) {
-  if (wf && necho == 6) return fm::k_setup<T, 6, true>;  // the water-fat echo count of the paper's experiments
-  if (wf) return lmax <= 4 ? fm::k_setup<T, 4, true> : (lmax <= 8 ? fm::k_setup<T, 8, true> : fm::k_setup<T, 16, true>);
+  if (wf) {  // 2-6 echoes: the exact count, by which the sweep's recurrence is unrolled
+    switch (necho) {
+      case 2: return fm::k_setup<T, 2, true>;
+      case 3: return fm::k_setup<T, 3, true>;
+      case 4: return fm::k_setup<T, 4, true>;
+      case 5: return fm::k_setup<T, 5, true>;
+      case 6: return fm::k_setup<T, 6, true>;
+      default: return lmax <= 8 ? fm::k_setup<T, 8, true> : fm::k_setup<T, 16, true>;
+    }
+  }
   // the field-map model with 2-4 echoes: the exact echo count, so no echo slot is loaded or summed for nothing
   if (necho == 2) return fm::k_setup<T, 2, false>;
   if (necho == 3) return fm::k_setup<T, 3, false>;
@@ -241,6 +250,14 @@ std::vector<fm::PairC<T>> make_pairs(const fm_params &p, const std::vector<std::
       out.push_back(q);
     }
   return out;
+}
+
+// The water-fat sweep covers [-|df|/2, |df|/2], df the offset of the largest fat peak.
+double sweep_half(const fm_params &p) {
+  int big = 0;
+  for (int q = 1; q < p.npeak; ++q)
+    if (p.fat_amp[q] > p.fat_amp[big]) big = q;
+  return std::fabs(p.fat_hz[big]) / 2.0;
 }
 
 // Arguments of chain launch number q (state and partial-sum slots by parity).
@@ -1460,6 +1477,7 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
     FM_ALLOC(p->rho, sizeof(double) * n);
     FM_ALLOC(p->gabs, sizeof(double) * L * L);
     FM_ALLOC(p->wf_tmp, sizeof(double) * n * 4);
+    FM_ALLOC(p->sweep_rot, sizeof(double2) * L * L);
   }
 #undef FM_ALLOC
 #undef FM_ALLOC_PAD
@@ -1488,6 +1506,15 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
     for (size_t i = 0; i < ga.size(); ++i) ga[i] = std::abs(G[i]);
     if (hipMemcpy(p->gabs, ga.data(), sizeof(double) * ga.size(), hipMemcpyHostToDevice) != hipSuccess)
       return cleanup(fail(FM_ERR_HIP, "upload of |Gamma| failed"));
+    std::vector<double2> rot;
+    const double step = 2.0 * sweep_half(*prm) / (prm->nsweep - 1);
+    for (int m = 0; m < prm->necho; ++m)
+      for (int q = m + 1; q < prm->necho; ++q) {
+        const double d = 6.283185307179586476925286766559 * (prm->te[m] - prm->te[q]) * step;
+        rot.push_back(make_double2(std::cos(d), std::sin(d)));
+      }
+    if (hipMemcpy(p->sweep_rot, rot.data(), sizeof(double2) * rot.size(), hipMemcpyHostToDevice) != hipSuccess)
+      return cleanup(fail(FM_ERR_HIP, "upload of the sweep rotations failed"));
   }
   if (hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking) != hipSuccess)
     return cleanup(fail(FM_ERR_HIP, "hipStreamCreate failed"));
@@ -1578,12 +1605,9 @@ fm_status setup_launch(fm_plan *p, const void *y, const void *sens, const uint8_
     a.pairs_d = (const fm::PairC<double> *)p->pairs_d;
     a.npairs = p->npairs;
     if (p->prm.model == FM_WATERFAT) {
-      // sweep over [-|df|/2, |df|/2], df the offset of the largest fat peak
-      int big = 0;
-      for (int q = 1; q < p->prm.npeak; ++q)
-        if (p->prm.fat_amp[q] > p->prm.fat_amp[big]) big = q;
       a.nsweep = p->prm.nsweep;
-      a.sweep_half = std::fabs(p->prm.fat_hz[big]) / 2.0;
+      a.sweep_half = sweep_half(p->prm);
+      a.sweep_rot = p->sweep_rot;
       a.ftilde = p->wf_tmp;
     }
     a.partials = p->setup_part;
