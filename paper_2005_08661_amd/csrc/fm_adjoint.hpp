@@ -47,7 +47,8 @@ struct AdjArgs {
   T *V;            // solution v
   T *H;            // exact Hessian diagonal h_j (without beta deg)
   T *Dc;           // Huber curvature (the preconditioner's D)
-  double *hinv;    // 1 / (D + beta deg) for the red-black preconditioner
+  double *hinv;    // 1 / (D + beta deg) for the red-black preconditioner (pair passes: of the red voxels at j >> 1)
+  T *P;            // pair passes: p of the black voxels at j >> 1
   int32_t par;     // CG iteration parity
   int32_t nparts_in;
   int32_t nvals_in;
@@ -114,7 +115,10 @@ __global__ __launch_bounds__(kNT) void k_adj_setup(AdjArgs<T> a, const double *_
     a.H[j] = hess;
     a.V[j] = T(0);
     a.Dd[1][j] = T(0);
-    if (write_hinv) a.hinv[j] = hv;
+    if (write_hinv == 1)
+      a.hinv[j] = hv;
+    else if (write_hinv == 2 && (c & NB_SELF) && !(c & NB_BLACK))
+      a.hinv[j >> 1] = hv;
   }
   store_partials<1, kNT>(acc, a.pout);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -207,6 +211,157 @@ __global__ __launch_bounds__(kNT) void k_adj_dir(AdjArgs<T> a) {
   put_state(st, a.sout, PK_ADJ_CURV, gridDim.x);
 }
 
+// Red-black IC(0) with an even column length: a CG iteration in three passes.
+// As in the iteration (k_rb_black_pair, k_rb_red_dir_pair), the black pass yields
+// r^T M^{-1} r in full from the factored form, so the red pass forms the direction
+// of both colours and d^T H d over the edges of C from their red ends, and the
+// pass over p in between goes.  128x128x64 MIX, per CG iteration: black 11.7, red
+// 8.5 and direction 8.2 us -> black 8.0 and red + direction 8.0 us.
+template <typename T>
+__global__ __launch_bounds__(kNT) void k_adj_black_pair(AdjArgs<T> a) {
+  const Geo g = a.geo;
+  const T *__restrict__ r = a.R;
+  const double *__restrict__ hv = a.hinv;
+  const Offs of(g);
+  const int np = (int)(g.n >> 1), stride = (int)gridDim.x * kNT;
+  uint32_t cb, cr;
+  int jb;
+  T d0, r0, rr, rn[6];
+  double hr, hn[6];
+  auto load = [&](int q) {
+    const int j0 = 2 * (q < np ? q : np - 1);
+    const uint32_t c2 = *reinterpret_cast<const uint16_t *>(a.code + j0);
+    const uint32_t cA = q < np ? (c2 & 0xffu) : 0u, cB = q < np ? (c2 >> 8) : 0u;
+    const bool fb = first_is_black(cA, cB);
+    jb = fb ? j0 : j0 + 1;
+    cb = fb ? cA : cB;
+    cr = fb ? cB : cA;
+    const Duo<T> r2 = ld_duo(r, j0);
+    r0 = fb ? r2.v0 : r2.v1;
+    rr = fb ? r2.v1 : r2.v0;
+    hr = hv[j0 >> 1];
+    d0 = a.Dc[jb];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      rn[k] = r[jb + of.o[k]];
+      hn[k] = hv[(jb + of.o[k]) >> 1];  // a red neighbour: its pair's entry
+    }
+  };
+  int q = (int)blockIdx.x * kNT + (int)threadIdx.x;
+  if (q < np) load(q);
+  const State st = take_state<kNT, 1>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, nullptr, a.status);
+  const double beta = a.beta, b2 = a.beta * a.beta;
+  double acc[1] = {0.0};
+  int bad = 0;
+  if (!st.cg_done) {
+    for (; q < np; q += stride) {
+      if (cr & NB_SELF) acc[0] += (double)rr * ((double)rr * hr);
+      if (cb & NB_SELF) {
+        double sp = 0.0, sxv = 0.0;
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+          if (has_nb(cb, k)) {
+            sp += hn[k];
+            sxv += (double)rn[k] * hn[k];
+          }
+        const double piv = ((double)d0 + beta * nb_deg(cb)) - b2 * sp;
+        double ip = 1.0 / piv;
+        if (!(piv > 0.0)) {
+          bad = 1;
+          ip = 0.0;
+        }
+        const double yb = (double)r0 + beta * sxv, x = yb * ip;
+        a.P[jb >> 1] = (T)x;
+        acc[0] += yb * x;
+      }
+      if (q + stride < np) load(q + stride);
+    }
+  }
+  if (bad) set_status(a.status, 5);
+  store_partials<1, kNT>(acc, a.pout);
+  put_state(st, a.sout, PK_ADJ_RHO, gridDim.x);
+}
+
+// d = z + (rho / rho_prev) d_prev of both colours, z on the red ones from the
+// black pass's p; partial d^T H d = sum h d^2 + beta ||C d||^2.
+template <typename T>
+__global__ __launch_bounds__(kNT) void k_adj_red_dir_pair(AdjArgs<T> a) {
+  const Geo g = a.geo;
+  const T *__restrict__ dp = a.Dd[(a.par + 1) & 1];
+  T *__restrict__ dn = a.Dd[a.par & 1];
+  const T *__restrict__ p = a.P;
+  const Offs of(g);
+  const int np = (int)(g.n >> 1), stride = (int)gridDim.x * kNT;
+  uint32_t cb, cr;
+  bool fbk;
+  T rr, dr, db, hb, hh, pb, pn[6], dq[6];
+  double hr;
+  auto load = [&](int q) {
+    const int j0 = 2 * (q < np ? q : np - 1);
+    const uint32_t c2 = *reinterpret_cast<const uint16_t *>(a.code + j0);
+    const uint32_t cA = q < np ? (c2 & 0xffu) : 0u, cB = q < np ? (c2 >> 8) : 0u;
+    const bool fb = first_is_black(cA, cB);
+    const int jr = fb ? j0 + 1 : j0;
+    fbk = fb;
+    cb = fb ? cA : cB;
+    cr = fb ? cB : cA;
+    const Duo<T> d2 = ld_duo(dp, j0), h2 = ld_duo(a.H, j0);
+    dr = fb ? d2.v1 : d2.v0;
+    db = fb ? d2.v0 : d2.v1;
+    hh = fb ? h2.v1 : h2.v0;
+    hb = fb ? h2.v0 : h2.v1;
+    pb = p[j0 >> 1];
+    rr = a.R[jr];
+    hr = a.hinv[j0 >> 1];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      pn[k] = p[(jr + of.o[k]) >> 1];  // a black neighbour: its pair's entry
+      dq[k] = dp[jr + of.o[k]];
+    }
+  };
+  int q = (int)blockIdx.x * kNT + (int)threadIdx.x;
+  if (q < np) load(q);
+  State st = take_state<kNT, 1>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, nullptr, a.status);
+  double acc[1] = {0.0};
+  int bad = 0;
+  if (!st.cg_done) {
+    const double rho = st.gtp, beta = a.beta;
+    const T bcg = (T)((st.cg_it > 0 && st.cg_rho_prev != 0.0) ? rho / st.cg_rho_prev : 0.0);
+    st.cg_rho = rho;
+    for (; q < np; q += stride) {
+      T drv = T(0), dbv = T(0);
+      if (cr & NB_SELF) {
+        double sp = 0.0;
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+          if (has_nb(cr, k)) sp += (double)pn[k];
+        if (!(hr > 0.0)) bad = 1;
+        const T z = (T)((double)rr * hr + beta * sp * hr);
+        drv = z + bcg * dr;
+        acc[0] += (double)drv * (double)drv * (double)hh;
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+          if (has_nb(cr, k)) {
+            const double dd = (double)(drv - (pn[k] + bcg * dq[k]));
+            acc[0] += beta * (dd * dd);
+          }
+      }
+      if (cb & NB_SELF) {
+        dbv = pb + bcg * db;
+        acc[0] += (double)dbv * (double)dbv * (double)hb;
+      }
+      Duo<T> out;
+      out.v0 = fbk ? dbv : drv;
+      out.v1 = fbk ? drv : dbv;
+      *reinterpret_cast<Duo<T> *>(dn + 2 * q) = out;
+      if (q + stride < np) load(q + stride);
+    }
+  }
+  if (bad) set_status(a.status, 5);
+  store_partials<1, kNT>(acc, a.pout);
+  put_state(st, a.sout, PK_ADJ_CURV, gridDim.x);
+}
+
 // v += alpha d, r -= alpha H d; partial ||r||^2.
 template <typename T, bool R2>
 __global__ __launch_bounds__(kNT) void k_adj_update(AdjArgs<T> a) {
@@ -268,6 +423,67 @@ __global__ __launch_bounds__(kNT) void k_adj_update(AdjArgs<T> a) {
         acc[0] += (double)rj * (double)rj;
       }
       if (base + stride < n) load(base + stride);
+    }
+  }
+  store_partials<1, kNT>(acc, a.pout);
+  put_state(st, a.sout, PK_ADJ_UPD, gridDim.x);
+}
+
+// k_adj_update with four consecutive voxels of a column per thread (FP32, first
+// differences, nz a multiple of 4): 16-byte loads and stores, the same values.
+__global__ __launch_bounds__(kNT) void k_adj_update_q(AdjArgs<float> a) {
+  const Geo g = a.geo;
+  const float *__restrict__ d = a.Dd[a.par & 1];
+  const int nq = (int)(g.n >> 2), stride = (int)gridDim.x * kNT, sx = (int)g.sx, sy = (int)g.sy;
+  uint32_t c4;
+  float4 d4, h4, v4, r4, dx[2], dy[2];
+  float dzm, dzp;
+  auto ld4 = [](const float *p) { return *reinterpret_cast<const float4 *>(p); };
+  auto load = [&](int q) {
+    const int j = 4 * q;
+    c4 = *reinterpret_cast<const uint32_t *>(a.code + j);
+    d4 = ld4(d + j);
+    h4 = ld4(a.H + j);
+    v4 = ld4(a.V + j);
+    r4 = ld4(a.R + j);
+    dx[0] = ld4(d + j - sx);
+    dx[1] = ld4(d + j + sx);
+    dy[0] = ld4(d + j - sy);
+    dy[1] = ld4(d + j + sy);
+    dzm = d[j - 1];
+    dzp = d[j + 4];
+  };
+  int q = (int)blockIdx.x * kNT + (int)threadIdx.x;
+  if (q < nq) load(q);
+  const State st = take_state<kNT, 1>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, nullptr, a.status);
+  double acc[1] = {0.0};
+  if (!st.cg_done) {
+    const float alpha = (float)st.cg_alpha, beta = (float)a.beta;
+    for (; q < nq; q += stride) {
+      const int j = 4 * q;
+      const float dv[4] = {d4.x, d4.y, d4.z, d4.w}, hv[4] = {h4.x, h4.y, h4.z, h4.w};
+      const float xm[4] = {dx[0].x, dx[0].y, dx[0].z, dx[0].w}, xp[4] = {dx[1].x, dx[1].y, dx[1].z, dx[1].w};
+      const float ym[4] = {dy[0].x, dy[0].y, dy[0].z, dy[0].w}, yp[4] = {dy[1].x, dy[1].y, dy[1].z, dy[1].w};
+      float vo[4] = {v4.x, v4.y, v4.z, v4.w}, ro[4] = {r4.x, r4.y, r4.z, r4.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t cv = (c4 >> (8 * i)) & 0xffu;
+        const float dn[6] = {xm[i], xp[i], ym[i], yp[i], i > 0 ? dv[i > 0 ? i - 1 : 0] : dzm, i < 3 ? dv[i < 3 ? i + 1 : 3] : dzp};
+        float lap = 0.f;
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+          if (has_nb(cv, k)) lap += dv[i] - dn[k];
+        const float qj = hv[i] * dv[i] + beta * lap;
+        const float rj = ro[i] - alpha * qj;
+        if (cv & NB_SELF) {
+          vo[i] = vo[i] + alpha * dv[i];
+          ro[i] = rj;
+          acc[0] += (double)rj * (double)rj;
+        }
+      }
+      *reinterpret_cast<float4 *>(a.V + j) = make_float4(vo[0], vo[1], vo[2], vo[3]);
+      *reinterpret_cast<float4 *>(a.R + j) = make_float4(ro[0], ro[1], ro[2], ro[3]);
+      if (q + stride < nq) load(q + stride);
     }
   }
   store_partials<1, kNT>(acc, a.pout);

@@ -122,6 +122,8 @@ struct fm_plan {
   double *a_hinv = nullptr, *a_ipiv = nullptr, *a_part = nullptr;
   fm::State *aS = nullptr;
   int32_t *a_status = nullptr;
+  fm::State *a_host = nullptr;           // [2] pinned copies of the CG state, and the events that follow them
+  hipEvent_t a_copied[2] = {nullptr, nullptr};
   // resident schedule (one launch for many iterations)
   bool reg2 = false;           // second-order regulariser
   int32_t sched = FM_SCHED_AUTO;
@@ -871,6 +873,9 @@ void free_plan(fm_plan *p) {
     if (kv.second.first) (void)hipGraphDestroy(kv.second.first);
   }
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
+  for (hipEvent_t e : p->a_copied)
+    if (e) (void)hipEventDestroy(e);
+  if (p->a_host) (void)hipHostFree(p->a_host);
   for (void *b : p->bases)
     if (b) (void)hipFree(b);
   delete p;
@@ -1095,6 +1100,10 @@ fm_status adj_alloc(fm_plan *p) {
     fm_status fs = alloc_faces(p);  // its CG is preconditioned in natural order
     if (fs) return fs;
   }
+  if (!p->a_host && hipHostMalloc((void **)&p->a_host, sizeof(fm::State) * 2, hipHostMallocDefault) != hipSuccess)
+    return fail(FM_ERR_ALLOC, "pinned memory for the adjoint state failed");
+  for (hipEvent_t &e : p->a_copied)
+    if (!e) FM_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   p->adj_ready = true;
   return FM_OK;
 }
@@ -1117,6 +1126,7 @@ fm::AdjArgs<T> adj_args(fm_plan *p, uint64_t q, int par, int nparts_in, int nval
   a.H = (T *)p->aH;
   a.Dc = (T *)p->aDc;
   a.hinv = p->a_hinv;
+  a.P = (T *)p->aZ;
   a.par = par;
   a.nparts_in = nparts_in;
   a.nvals_in = nvals_in;
@@ -1163,10 +1173,31 @@ fm::IterArgs<T> adj_precond_args(fm_plan *p, uint64_t q, int nparts_in, int nval
   return a;
 }
 
+// The adjoint's CG iteration in three passes (red-black IC(0), even columns).
+bool adj_pairs(const fm_plan *p) {
+  return !p->reg2 && p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_REDBLACK && p->geo.nz % 2 == 0;
+}
+
 template <typename T>
 fm_status adj_enqueue_iteration(fm_plan *p, uint64_t &q, int &np, int &nv, int k, hipStream_t s) {
   const T *r = (const T *)p->aR;
   Recorder *rec = nullptr;
+  if (adj_pairs(p)) {
+    auto launch = [&](void (*kern)(fm::AdjArgs<T>)) -> fm_status {
+      hipLaunchKernelGGL(kern, dim3(p->sgrid), dim3(fm::kNT), 0, s, adj_args<T>(p, q++, k & 1, np, nv));
+      FM_LAUNCH_CHECK();
+      np = p->sgrid;
+      nv = 1;
+      return FM_OK;
+    };
+    fm_status e = launch(fm::k_adj_black_pair<T>);
+    if (!e) e = launch(fm::k_adj_red_dir_pair<T>);
+    if (e) return e;
+    if constexpr (std::is_same<T, float>::value)
+      return launch(p->geo.nz % 4 == 0 ? fm::k_adj_update_q : fm::k_adj_update<T, false>);
+    else
+      return launch(fm::k_adj_update<T, false>);
+  }
   if (p->reg2) {
     // second-order C: diag(H) with diag(C^T C) of the 13-point operator (also for IC(0) plans), or none
     FM_LAUNCH(0, fm::k_diag2<T>, dim3(p->sgrid), dim3(fm::kNT), s, adj_precond_args<T>(p, q++, np, nv), r,
@@ -1216,7 +1247,8 @@ fm_status adj_enqueue_iteration(fm_plan *p, uint64_t &q, int &np, int &nv, int k
   return FM_OK;
 }
 
-fm_status adj_finish(fm_plan *p, uint64_t &q, int &np, int &nv, fm::State *host, hipStream_t s) {
+// Consume the last pass's sums and copy the CG state to host slot `slot`.
+fm_status adj_finish(fm_plan *p, uint64_t &q, int &np, int &nv, int slot, hipStream_t s) {
   hipLaunchKernelGGL(fm::k_finish, dim3(1), dim3(kBlock), 0, s, (const fm::State *)(p->aS + (q & 1)),
                      p->aS + ((q + 1) & 1), (const double *)(p->a_part + (size_t)(q & 1) * p->part_rows * kMaxK),
                      np, nv, p->prm.beta, (double *)nullptr, p->a_status);
@@ -1224,8 +1256,8 @@ fm_status adj_finish(fm_plan *p, uint64_t &q, int &np, int &nv, fm::State *host,
   ++q;
   np = 0;
   nv = 0;
-  FM_HIP(hipMemcpyAsync(host, p->aS + (q & 1), sizeof(fm::State), hipMemcpyDeviceToHost, s));
-  FM_HIP(hipStreamSynchronize(s));
+  FM_HIP(hipMemcpyAsync(p->a_host + slot, p->aS + (q & 1), sizeof(fm::State), hipMemcpyDeviceToHost, s));
+  FM_HIP(hipEventRecord(p->a_copied[slot], s));
   return FM_OK;
 }
 
@@ -1237,26 +1269,33 @@ struct OpAdjoint {
                        double rtol, fm::State *out, hipStream_t s) {
     uint64_t q = 0;
     int np = 0, nv = 0;
-    const int write_hinv = (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_REDBLACK) ? 1 : 0;
+    const int write_hinv = adj_pairs(p) ? 2 : (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_REDBLACK) ? 1 : 0;
     hipLaunchKernelGGL((fm::k_adj_setup<T, LMAX>), dim3(p->sgrid), dim3(fm::kNT), 0, s, adj_args<T>(p, q++, 0, 0, 0),
                        dldf, rtol * rtol, write_hinv);
     FM_LAUNCH_CHECK();
     np = p->sgrid;
     nv = 1;
-    fm::State st{};
-    int k = 0;
+    // The state after a chunk is looked at once the next chunk is in the stream, so
+    // the GPU does not wait for the host (passes after convergence do nothing).
+    int k = 0, slot = 0;
+    bool pending = false;
     while (k < maxit) {
       const int chunk = (maxit - k) < kAdjCheck ? (maxit - k) : kAdjCheck;
       for (int i = 0; i < chunk; ++i, ++k) {
         fm_status e = adj_enqueue_iteration<T>(p, q, np, nv, k, s);
         if (e) return e;
       }
-      fm_status e = adj_finish(p, q, np, nv, &st, s);
+      fm_status e = adj_finish(p, q, np, nv, slot, s);
       if (e) return e;
-      if (st.cg_done) break;
+      if (pending) {
+        FM_HIP(hipEventSynchronize(p->a_copied[slot ^ 1]));
+        if (p->a_host[slot ^ 1].cg_done) break;
+      }
+      pending = true;
+      slot ^= 1;
     }
     if (maxit == 0) {
-      fm_status e = adj_finish(p, q, np, nv, &st, s);
+      fm_status e = adj_finish(p, q, np, nv, 0, s);
       if (e) return e;
     }
     if (p->reg2)
@@ -1268,9 +1307,10 @@ struct OpAdjoint {
     FM_LAUNCH_CHECK();
     np = p->sgrid;
     nv = 1;
-    fm_status e = adj_finish(p, q, np, nv, &st, s);
+    fm_status e = adj_finish(p, q, np, nv, 0, s);
     if (e) return e;
-    *out = st;
+    FM_HIP(hipStreamSynchronize(s));
+    *out = p->a_host[0];
     return FM_OK;
   }
 };
