@@ -105,7 +105,7 @@ __global__ __launch_bounds__(kNT) void k_adj_setup(AdjArgs<T> a, const double *_
       T rho[LMAX], tau[LMAX];
       load_echoes<T, LMAX>(a.dat, (int64_t)n, j, a.L, rho, tau);
       voxel_curvatures<T, LMAX>(rho, tau, a.L, a.pairs, a.F[j], curv, hess);
-      r = (T)dldf[j];
+      r = (T)dldf[g.user(j)];
       const double h = (double)curv + a.beta * nb_deg(c);
       hv = h > 0.0 ? 1.0 / h : 0.0;
       acc[0] += (double)r * (double)r;
@@ -502,7 +502,9 @@ __global__ __launch_bounds__(kNT) void k_adj_out(AdjArgs<T> a, const float2 *__r
   for (int j = (int)blockIdx.x * kNT + (int)threadIdx.x; j < n; j += (int)gridDim.x * kNT) {
     const uint32_t c = a.code[j];
     const T vj = (c & NB_SELF) ? a.V[j] : T(0);
-    if (vout) vout[j] = (double)vj;
+    const int64_t u = g.user(j), nu = g.user_n();
+    if (u < 0) continue;  // never in the mask
+    if (vout) vout[u] = (double)vj;
     // zhat-gradients in the frame of each echo's own phase: dL/dzhat_l = a_l e^{i theta_l}
     T are[LMAX], aim[LMAX];
 #pragma unroll
@@ -573,7 +575,7 @@ __global__ __launch_bounds__(kNT) void k_adj_out(AdjArgs<T> a, const float2 *__r
       if (sens) {
         ss = 0.0;
         for (int cc = 0; cc < ncoil; ++cc) {
-          const float2 sv = sens[(int64_t)cc * n + j];
+          const float2 sv = sens[(int64_t)cc * nu + u];
           ss += (double)sv.x * sv.x + (double)sv.y * sv.y;
         }
       }
@@ -581,7 +583,7 @@ __global__ __launch_bounds__(kNT) void k_adj_out(AdjArgs<T> a, const float2 *__r
       for (int cc = 0; cc < ncoil; ++cc) {
         double sr = scale, si = 0.0;
         if (sens) {
-          const float2 sv = sens[(int64_t)cc * n + j];
+          const float2 sv = sens[(int64_t)cc * nu + u];
           sr = sv.x * scale;
           si = sv.y * scale;
         }
@@ -596,7 +598,7 @@ __global__ __launch_bounds__(kNT) void k_adj_out(AdjArgs<T> a, const float2 *__r
           float2 o;
           o.x = (float)(sr * (double)xr - si * (double)xim);
           o.y = (float)(sr * (double)xim + si * (double)xr);
-          dldy[((int64_t)cc * a.L + l) * n + j] = o;
+          dldy[((int64_t)cc * a.L + l) * nu + u] = o;
         }
       }
     }

@@ -1002,6 +1002,39 @@ bool plan_resident(fm_plan *p) {
   return true;
 }
 
+// The plan's arrays with columns of nz >= prm.nz voxels.
+void plan_geometry(fm_plan *p, int32_t nz) {
+  const fm_params &q = p->prm;
+  p->geo.nx = q.nx;
+  p->geo.ny = q.ny;
+  p->geo.nz = nz;
+  p->geo.uz = q.nz;
+  p->geo.sy = nz;
+  p->geo.sx = (int64_t)q.ny * nz;
+  p->geo.n = p->n = (int64_t)q.nx * q.ny * nz;
+  // one x-plane of guard entries on each side (two for the second-order stencil's +-2 neighbours)
+  p->pad = (((p->reg2 ? 2 : 1) * p->geo.sx + 63) / 64) * 64;
+}
+
+// Column length of the plan's arrays.  The pair and tile passes of red-black IC(0) need an even
+// one, the 16-byte-load passes (FP32, up to 6 echoes) a multiple of 4; a column is lengthened to
+// it with voxels outside the mask where that adds at most an eighth (beyond, the added bytes
+// cost more than the per-voxel passes: 10 -> 12 would add a fifth).  91x109x91, F64, 40
+// iterations: 3.97 -> 3.61 ms; drawn odd sizes 3.31 -> 2.59 and 2.91 -> 2.39 ms.  Plans that
+// qualify for the resident schedule need no more than the even length they have, orders with
+// arrays of their own (natural, block red-black, three colours, IC_t) keep the caller's, and so
+// do volumes beyond 2^26 voxels, where the memory would be missed.
+int32_t padded_columns(const fm_plan *p) {
+  const fm_params &q = p->prm;
+  const bool rb = q.precond == FM_PRECOND_IC0 && q.ordering == FM_ORDER_REDBLACK;
+  const bool none = q.precond == FM_PRECOND_DIAG || q.precond == FM_PRECOND_NONE;
+  if (p->reg2 || p->res_ok || !(rb || none) || p->n > ((int64_t)1 << 26)) return q.nz;
+  const int32_t up4 = (q.nz + 3) / 4 * 4, up2 = (q.nz + 1) / 2 * 2;
+  if (p->mix && q.necho <= 6 && 8 * (up4 - q.nz) <= q.nz) return up4;
+  if (rb && 8 * (up2 - q.nz) <= q.nz) return up2;
+  return q.nz;
+}
+
 fm_status run_graph(fm_plan *p, int niter, hipStream_t s);
 
 fm_status run_iterations(fm_plan *p, int niter, hipStream_t s) {
@@ -1054,10 +1087,11 @@ fm_status run_graph(fm_plan *p, int niter, hipStream_t s) {
 
 template <typename T>
 fm_status enqueue_start(fm_plan *p, const double *f0, hipStream_t s) {
+  const int user_f0 = f0 != p->f0buf;
   p->iter_host = 0;
   set_parts(p, 0, 0);
   const uint64_t q = p->q++;
-  hipLaunchKernelGGL(fm::k_start<T>, dim3(p->grid), dim3(kBlock), 0, s, p->geo, f0, (const uint8_t *)p->code,
+  hipLaunchKernelGGL(fm::k_start<T>, dim3(p->grid), dim3(kBlock), 0, s, p->geo, f0, user_f0, (const uint8_t *)p->code,
                      (T *)p->F[1], (T *)p->Z[1], (T *)p->G[1], p->cm ? p->cm_elems : p->n, p->S + ((q + 1) & 1),
                      p->prm.niter, p->prm.nmls, (const double *)p->nmask);
   FM_LAUNCH_CHECK();
@@ -1348,16 +1382,18 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
   if (vs) return vs;
   fm_plan *p = new fm_plan();
   p->prm = *prm;
-  p->n = (int64_t)prm->nx * prm->ny * prm->nz;
-  p->geo.nx = prm->nx;
-  p->geo.ny = prm->ny;
-  p->geo.nz = prm->nz;
-  p->geo.n = p->n;
-  p->geo.sy = prm->nz;
-  p->geo.sx = (int64_t)prm->ny * prm->nz;
+  p->mix = prm->precision == FM_PREC_MIX;
+  p->tsize = p->mix ? sizeof(float) : sizeof(double);
   p->reg2 = prm->reg_order == 2;
-  // one x-plane of guard entries on each side (two for the second-order stencil's +-2 neighbours)
-  p->pad = (((p->reg2 ? 2 : 1) * p->geo.sx + 63) / 64) * 64;
+  if (hipGetDevice(&p->device) != hipSuccess) {
+    delete p;
+    return fail(FM_ERR_HIP, "hipGetDevice failed");
+  }
+  plan_geometry(p, prm->nz);
+  p->res_ok = plan_resident(p);
+  const int32_t nzp = padded_columns(p);
+  plan_geometry(p, nzp);
+  if (nzp != prm->nz && p->n + 2 * p->pad >= ((int64_t)1 << 31)) plan_geometry(p, prm->nz);
   p->cm = p->reg2 && prm->precond == FM_PRECOND_IC0;
   if (p->cm) {
     const int64_t m = ((int64_t)prm->nz + 2) / 3;
@@ -1367,8 +1403,6 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
     delete p;
     return fail(FM_ERR_SHAPE, "volume too large for 32-bit voxel indices");
   }
-  p->mix = prm->precision == FM_PREC_MIX;
-  p->tsize = p->mix ? sizeof(float) : sizeof(double);
   p->lmax = prm->necho <= 4 ? 4 : (prm->necho <= 8 ? 8 : 16);
   const int64_t blocks = (p->n + kBlock - 1) / kBlock;
   p->grid = (int)(blocks < kMaxGrid ? blocks : kMaxGrid);
@@ -1381,7 +1415,6 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
     free_plan(p);
     return st;
   };
-  if (hipGetDevice(&p->device) != hipSuccess) return cleanup(fail(FM_ERR_HIP, "hipGetDevice failed"));
   const size_t n = (size_t)p->n, ts = p->tsize, L = (size_t)prm->necho;
   const size_t trace_bytes = sizeof(double) * FM_TR_W * ((size_t)prm->niter + 1);
 #define FM_ALLOC(ptr, bytes)                                                          \
@@ -1479,7 +1512,6 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
   FM_ALLOC(p->status, sizeof(int32_t));
   FM_ALLOC(p->trace, trace_bytes);
   FM_ALLOC(p->f0buf, sizeof(double) * n);
-  p->res_ok = plan_resident(p);
   if (p->res_ok) {
     FM_ALLOC(p->res_part, sizeof(double) * fm::kResSlots * kMaxK * (size_t)p->res_grid);
     FM_ALLOC(p->res_bar, res_bar_bytes(p));
@@ -1676,7 +1708,16 @@ fm_status fm_init(fm_plan *p, double *f0, hipStream_t s) {
   if (cs) return cs;
   if (!f0) return fail(FM_ERR_ARG, "f0 must not be NULL");
   if (!p->setup_done) return fail(FM_ERR_STATE, "fm_init needs fm_setup first");
-  if (p->prm.model == FM_WATERFAT) return wf_init(p, f0, s);
+  const bool padded = p->geo.uz != p->geo.nz;
+  if (p->prm.model == FM_WATERFAT) {
+    fm_status st = wf_init(p, padded ? p->f0buf : f0, s);
+    if (st || !padded) return st;
+  }
+  if (padded) {
+    hipLaunchKernelGGL(fm::k_from_work<double>, dim3(p->grid), dim3(kBlock), 0, s, p->geo, (const double *)p->f0buf, f0);
+    FM_LAUNCH_CHECK();
+    return FM_OK;
+  }
   FM_HIP(hipMemcpyAsync(f0, p->f0buf, sizeof(double) * p->n, hipMemcpyDeviceToDevice, s));
   return FM_OK;
 }
@@ -1704,9 +1745,9 @@ fm_status fm_precondition(fm_plan *p, const double *curv, const double *g, doubl
       hipLaunchKernelGGL(fm::k_to_cm<T>, dim3(p->grid), dim3(kBlock), 0, s, p->geo, g, (T *)p->G[0]);
       FM_LAUNCH_CHECK();
     } else {
-      hipLaunchKernelGGL(fm::k_to_work<T>, dim3(p->grid), dim3(kBlock), 0, s, p->n, curv, (T *)p->D);
+      hipLaunchKernelGGL(fm::k_to_work<T>, dim3(p->grid), dim3(kBlock), 0, s, p->geo, curv, (T *)p->D);
       FM_LAUNCH_CHECK();
-      hipLaunchKernelGGL(fm::k_to_work<T>, dim3(p->grid), dim3(kBlock), 0, s, p->n, g, (T *)p->G[0]);
+      hipLaunchKernelGGL(fm::k_to_work<T>, dim3(p->grid), dim3(kBlock), 0, s, p->geo, g, (T *)p->G[0]);
       FM_LAUNCH_CHECK();
     }
     FM_HIP(hipMemsetAsync(p->status, 0, sizeof(int32_t), s));
@@ -1730,7 +1771,7 @@ fm_status fm_precondition(fm_plan *p, const double *curv, const double *g, doubl
         FM_LAUNCH_CHECK();
       }
     } else {
-      hipLaunchKernelGGL(fm::k_from_work<T>, dim3(p->grid), dim3(kBlock), 0, s, p->n, (const T *)p->P, pout);
+      hipLaunchKernelGGL(fm::k_from_work<T>, dim3(p->grid), dim3(kBlock), 0, s, p->geo, (const T *)p->P, pout);
       FM_LAUNCH_CHECK();
       if (piv && p->ict_tiled) {
         if (p->prm.ict_level == 0)
@@ -1745,7 +1786,7 @@ fm_status fm_precondition(fm_plan *p, const double *curv, const double *g, doubl
                            (const double *)p->ict_ld, piv);
         FM_LAUNCH_CHECK();
       } else if (piv) {
-        hipLaunchKernelGGL(fm::k_pivots, dim3(p->grid), dim3(kBlock), 0, s, p->n, (const double *)p->ipiv, piv);
+        hipLaunchKernelGGL(fm::k_pivots, dim3(p->grid), dim3(kBlock), 0, s, p->geo, (const double *)p->ipiv, piv);
         FM_LAUNCH_CHECK();
       }
     }

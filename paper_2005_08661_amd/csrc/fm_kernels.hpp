@@ -22,6 +22,17 @@ struct Geo {
   int32_t nx, ny, nz;
   int64_t n;
   int64_t sx, sy;  // strides of x and y (z stride is 1)
+  // The caller's arrays have columns of uz <= nz voxels; the nz - uz last voxels of a column
+  // exist only in the plan's arrays and are never in the mask.
+  int32_t uz;
+  __device__ __forceinline__ int64_t user_sx() const { return (int64_t)ny * uz; }
+  __device__ __forceinline__ int64_t user_n() const { return (int64_t)nx * ny * uz; }
+  // Index of voxel j in the caller's arrays, -1 if it has none (volumes of fewer than 2^31 voxels).
+  __device__ __forceinline__ int64_t user(int64_t j) const {
+    if (uz == nz) return j;
+    const uint32_t col = (uint32_t)j / (uint32_t)nz, z = (uint32_t)j - col * (uint32_t)nz;
+    return z < (uint32_t)uz ? (int64_t)col * uz + z : -1;
+  }
 };
 
 // ---------------------------------------------------------------------------
@@ -33,8 +44,8 @@ template <typename T>
 struct SetupArgs {
   Geo geo;
   int32_t ncoil, L;
-  const float2 *y;     // [ncoil][L][n]
-  const float2 *sens;  // [ncoil][n] or nullptr
+  const float2 *y;     // [ncoil][L][user n]
+  const float2 *sens;  // [ncoil][user n] or nullptr
   const uint8_t *mask;
   T2<T> *dat;          // [L][estride] (|zhat|, angle/2pi)
   int64_t estride;     // echo stride of dat (n, or the batch's padded total)
@@ -63,17 +74,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LMAX <= 
     const int32_t z = (int32_t)(j % g.nz);
     const int32_t yy = (int32_t)((j / g.nz) % g.ny);
     const int32_t x = (int32_t)(j / g.sx);
-    const bool in = a.mask[j] != 0;
+    const bool own = z < g.uz;  // the caller's arrays hold this voxel
+    const int64_t col = (int64_t)x * g.ny + yy, ju = col * g.uz + (own ? z : 0), sxu = g.user_sx(), nu = g.user_n();
+    const bool in = own && a.mask[ju] != 0;
     uint32_t c = 0;
     if (in) {
       c = NB_SELF;
       if ((x + yy + z) & 1) c |= NB_BLACK;
-      if (x > 0 && a.mask[j - g.sx]) c |= NB_XM;
-      if (x < g.nx - 1 && a.mask[j + g.sx]) c |= NB_XP;
-      if (yy > 0 && a.mask[j - g.sy]) c |= NB_YM;
-      if (yy < g.ny - 1 && a.mask[j + g.sy]) c |= NB_YP;
-      if (z > 0 && a.mask[j - 1]) c |= NB_ZM;
-      if (z < g.nz - 1 && a.mask[j + 1]) c |= NB_ZP;
+      if (x > 0 && a.mask[ju - sxu]) c |= NB_XM;
+      if (x < g.nx - 1 && a.mask[ju + sxu]) c |= NB_XP;
+      if (yy > 0 && a.mask[ju - g.uz]) c |= NB_YM;
+      if (yy < g.ny - 1 && a.mask[ju + g.uz]) c |= NB_YP;
+      if (z > 0 && a.mask[ju - 1]) c |= NB_ZM;
+      if (z < g.uz - 1 && a.mask[ju + 1]) c |= NB_ZP;
       cnt[0] += 1.0;
     }
     a.code[j] = (uint8_t)c;
@@ -93,9 +106,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LMAX <= 
 #pragma unroll
       for (int u = 0; u < CU; ++u) {
         const int cc = c0 + u < a.ncoil ? c0 + u : c0;
-        sv[u] = a.sens ? a.sens[(int64_t)cc * g.n + j] : make_float2(1.f, 0.f);
+        sv[u] = a.sens ? a.sens[(int64_t)cc * nu + ju] : make_float2(1.f, 0.f);
 #pragma unroll
-        for (int l = 0; l < LMAX; ++l) yv[u][l] = a.y[((int64_t)cc * a.L + (l < a.L ? l : 0)) * g.n + j];
+        for (int l = 0; l < LMAX; ++l) yv[u][l] = a.y[((int64_t)cc * a.L + (l < a.L ? l : 0)) * nu + ju];
       }
 #pragma unroll
       for (int u = 0; u < CU; ++u) {
@@ -275,14 +288,14 @@ __device__ __forceinline__ void init_state(State *sout, int trace_cap, int nmls,
 
 // Start of a solve: fresh state and the initial map in F[1] (the slot read as
 // the previous iterate by the first gradient pass), zero previous direction
-// and gradient.
+// and gradient.  f0 is laid out like the caller's arrays (user_f0) or the plan's.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_start(Geo g, const double *__restrict__ f0,
+__global__ __launch_bounds__(kBlock) void k_start(Geo g, const double *__restrict__ f0, int user_f0,
                                                    const uint8_t *__restrict__ code, T *Fprev,
                                                    T *Zprev, T *Gprev, int64_t gcount, State *sout, int trace_cap,
                                                    int nmls, const double *nmask) {
   for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < g.n; j += (int64_t)gridDim.x * kBlock) {
-    Fprev[j] = (code[j] & NB_SELF) ? (T)f0[j] : T(0);
+    Fprev[j] = (code[j] & NB_SELF) ? (T)f0[user_f0 ? g.user(j) : j] : T(0);
     Zprev[j] = T(0);
   }
   // gcount elements of the gradient (more than n in the colour-major layout)
@@ -471,44 +484,46 @@ __global__ __launch_bounds__(kBlock) void k_eval(IterArgs<T> a, const double *__
   const Geo g = a.geo;
   for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < g.n; j += (int64_t)gridDim.x * kBlock) {
     const uint32_t c = a.code[j];
+    const int64_t u = g.user(j), sxu = g.user_sx(), syu = g.uz;
+    if (u < 0) continue;
     if (!(c & NB_SELF)) {
-      if (phi_o) phi_o[j] = 0.0;
-      if (dphi_o) dphi_o[j] = 0.0;
-      if (curv_o) curv_o[j] = 0.0;
-      if (lap_o) lap_o[j] = 0.0;
+      if (phi_o) phi_o[u] = 0.0;
+      if (dphi_o) dphi_o[u] = 0.0;
+      if (curv_o) curv_o[u] = 0.0;
+      if (lap_o) lap_o[u] = 0.0;
       continue;
     }
-    const T fj = (T)fu[j];
+    const T fj = (T)fu[u];
     T lap = T(0);
     if (a.reg2) {
       // second-order C^T C (13-point): rows centred at j and at its axis neighbours
-      const int64_t s3[3] = {g.sx, g.sy, 1};
+      const int64_t s3[3] = {g.sx, g.sy, 1}, u3[3] = {sxu, syu, 1};
 #pragma unroll
       for (int ax = 0; ax < 3; ++ax) {
-        const int64_t s = s3[ax];
+        const int64_t s = s3[ax], us = u3[ax];
         const bool hm = (c >> (2 * ax + 1)) & 1u, hp = (c >> (2 * ax + 2)) & 1u;
         const bool r = hm && hp;
         const bool rm = hm && row2_code(a.code[j - s], ax), rp = hp && row2_code(a.code[j + s], ax);
-        if (r) lap += T(-2) * ((T)fu[j - s] - T(2) * fj + (T)fu[j + s]);
-        if (rp) lap += fj - T(2) * (T)fu[j + s] + (T)fu[j + 2 * s];
-        if (rm) lap += (T)fu[j - 2 * s] - T(2) * (T)fu[j - s] + fj;
+        if (r) lap += T(-2) * ((T)fu[u - us] - T(2) * fj + (T)fu[u + us]);
+        if (rp) lap += fj - T(2) * (T)fu[u + us] + (T)fu[u + 2 * us];
+        if (rm) lap += (T)fu[u - 2 * us] - T(2) * (T)fu[u - us] + fj;
       }
     } else {
-      if (c & NB_XM) lap += fj - (T)fu[j - g.sx];
-      if (c & NB_XP) lap += fj - (T)fu[j + g.sx];
-      if (c & NB_YM) lap += fj - (T)fu[j - g.sy];
-      if (c & NB_YP) lap += fj - (T)fu[j + g.sy];
-      if (c & NB_ZM) lap += fj - (T)fu[j - 1];
-      if (c & NB_ZP) lap += fj - (T)fu[j + 1];
+      if (c & NB_XM) lap += fj - (T)fu[u - sxu];
+      if (c & NB_XP) lap += fj - (T)fu[u + sxu];
+      if (c & NB_YM) lap += fj - (T)fu[u - syu];
+      if (c & NB_YP) lap += fj - (T)fu[u + syu];
+      if (c & NB_ZM) lap += fj - (T)fu[u - 1];
+      if (c & NB_ZP) lap += fj - (T)fu[u + 1];
     }
     T rho[LMAX], tau[LMAX];
     load_echoes<T, LMAX>(a.dat, g.n, (int)j, a.L, rho, tau);
     T phi, dphi, curv;
     voxel_terms<T, LMAX>(rho, tau, a.L, a.pairs, fj, phi, dphi, curv);
-    if (phi_o) phi_o[j] = (double)phi;
-    if (dphi_o) dphi_o[j] = (double)dphi;
-    if (curv_o) curv_o[j] = (double)curv;
-    if (lap_o) lap_o[j] = (double)lap;
+    if (phi_o) phi_o[u] = (double)phi;
+    if (dphi_o) dphi_o[u] = (double)dphi;
+    if (curv_o) curv_o[u] = (double)curv;
+    if (lap_o) lap_o[u] = (double)lap;
   }
 }
 
@@ -525,24 +540,26 @@ __global__ __launch_bounds__(kBlock) void k_components(Geo g, int ncoil, int L, 
                                                         const T *__restrict__ fw, const double *__restrict__ te,
                                                         const double2 *__restrict__ B, float2 *__restrict__ out) {
   for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < g.n; j += (int64_t)gridDim.x * kBlock) {
+    const int64_t u = g.user(j), nu = g.user_n();
+    if (u < 0) continue;
     double xr[2] = {0.0, 0.0}, xi[2] = {0.0, 0.0};
     if (code[j] & NB_SELF) {
       double ss = 1.0;
       if (sens) {
         ss = 0.0;
         for (int c = 0; c < ncoil; ++c) {
-          const float2 sv = sens[(int64_t)c * g.n + j];
+          const float2 sv = sens[(int64_t)c * nu + u];
           ss += (double)sv.x * sv.x + (double)sv.y * sv.y;
         }
       }
       if (ss > 0.0) {
-        const double fj = fu ? fu[j] : (double)fw[j];
+        const double fj = fu ? fu[u] : (double)fw[j];
         for (int l = 0; l < L; ++l) {
           double zr = 0.0, zi = 0.0;
           for (int c = 0; c < ncoil; ++c) {
-            const float2 yv = y[((int64_t)c * L + l) * g.n + j];
+            const float2 yv = y[((int64_t)c * L + l) * nu + u];
             if (sens) {
-              const float2 sv = sens[(int64_t)c * g.n + j];
+              const float2 sv = sens[(int64_t)c * nu + u];
               zr += (double)sv.x * yv.x + (double)sv.y * yv.y;
               zi += (double)sv.x * yv.y - (double)sv.y * yv.x;
             } else {
@@ -570,27 +587,33 @@ __global__ __launch_bounds__(kBlock) void k_components(Geo g, int ncoil, int L, 
       float2 o;
       o.x = (float)xr[k];
       o.y = (float)xi[k];
-      out[(int64_t)k * g.n + j] = o;
+      out[(int64_t)k * nu + u] = o;
     }
   }
 }
 
 // Conversions between user float64 arrays and the working type.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_to_work(int64_t n, const double *__restrict__ src, T *dst) {
-  for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n; j += (int64_t)gridDim.x * kBlock)
-    dst[j] = (T)src[j];
+__global__ __launch_bounds__(kBlock) void k_to_work(Geo g, const double *__restrict__ src, T *dst) {
+  for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < g.n; j += (int64_t)gridDim.x * kBlock) {
+    const int64_t u = g.user(j);
+    dst[j] = u >= 0 ? (T)src[u] : T(0);
+  }
 }
 
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_from_work(int64_t n, const T *__restrict__ src, double *dst) {
-  for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n; j += (int64_t)gridDim.x * kBlock)
-    dst[j] = (double)src[j];
+__global__ __launch_bounds__(kBlock) void k_from_work(Geo g, const T *__restrict__ src, double *dst) {
+  for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < g.n; j += (int64_t)gridDim.x * kBlock) {
+    const int64_t u = g.user(j);
+    if (u >= 0) dst[u] = (double)src[j];
+  }
 }
 
-__global__ __launch_bounds__(kBlock) void k_pivots(int64_t n, const double *__restrict__ ipiv, double *piv) {
-  for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n; j += (int64_t)gridDim.x * kBlock)
-    piv[j] = ipiv[j] > 0.0 ? 1.0 / ipiv[j] : 0.0;
+__global__ __launch_bounds__(kBlock) void k_pivots(Geo g, const double *__restrict__ ipiv, double *piv) {
+  for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < g.n; j += (int64_t)gridDim.x * kBlock) {
+    const int64_t u = g.user(j);
+    if (u >= 0) piv[u] = ipiv[j] > 0.0 ? 1.0 / ipiv[j] : 0.0;
+  }
 }
 
 }  // namespace fm

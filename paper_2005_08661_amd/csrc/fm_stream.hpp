@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kNT) void k_grad(IterArgs<T> a0) {
       const uint32_t cv = c[v];
       if (!(cv & NB_SELF)) {
         fo[j] = T(0);
-        if (a.fout) a.fout[j] = 0.0;
+        if (const int64_t u = a.fout ? g.user(j) : -1; u >= 0) a.fout[u] = 0.0;
         if (!a.final_pass) {
           gg[j] = T(0);
           a.D[j] = T(0);
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kNT) void k_grad(IterArgs<T> a0) {
       voxel_terms<T, LMAX>(rho[v], tau[v], a.L, a.pairs, fj, phi, dphi, curv);
       const T gj = dphi + beta * lap;
       fo[j] = fj;
-      if (a.fout) a.fout[j] = (double)fj;
+      if (a.fout) a.fout[g.user(j)] = (double)fj;
       if (!a.final_pass) {
         gg[j] = gj;
         a.D[j] = curv;
