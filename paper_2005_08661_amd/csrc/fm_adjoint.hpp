@@ -250,6 +250,7 @@ __global__ __launch_bounds__(kNT) void k_adj_black_pair(AdjArgs<T> a) {
   int q = (int)blockIdx.x * kNT + (int)threadIdx.x;
   if (q < np) load(q);
   const State st = take_state<kNT, 1>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, nullptr, a.status);
+  put_state(st, a.sout, PK_ADJ_RHO, gridDim.x);
   const double beta = a.beta, b2 = a.beta * a.beta;
   double acc[1] = {0.0};
   int bad = 0;
@@ -279,7 +280,6 @@ __global__ __launch_bounds__(kNT) void k_adj_black_pair(AdjArgs<T> a) {
   }
   if (bad) set_status(a.status, 5);
   store_partials<1, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_ADJ_RHO, gridDim.x);
 }
 
 // d = z + (rho / rho_prev) d_prev of both colours, z on the red ones from the
@@ -396,6 +396,7 @@ __global__ __launch_bounds__(kNT) void k_adj_update(AdjArgs<T> a) {
   int base = (int)blockIdx.x * chunk;
   if (base < n) load(base);
   const State st = take_state<kNT, 1>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, nullptr, a.status);
+  put_state(st, a.sout, PK_ADJ_UPD, gridDim.x);
   double acc[1] = {0.0};
   if (!st.cg_done) {
     const T alpha = (T)st.cg_alpha;
@@ -426,7 +427,6 @@ __global__ __launch_bounds__(kNT) void k_adj_update(AdjArgs<T> a) {
     }
   }
   store_partials<1, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_ADJ_UPD, gridDim.x);
 }
 
 // k_adj_update with four consecutive voxels of a column per thread (FP32, first
@@ -456,6 +456,7 @@ __global__ __launch_bounds__(kNT) void k_adj_update_q(AdjArgs<float> a) {
   int q = (int)blockIdx.x * kNT + (int)threadIdx.x;
   if (q < nq) load(q);
   const State st = take_state<kNT, 1>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, nullptr, a.status);
+  put_state(st, a.sout, PK_ADJ_UPD, gridDim.x);
   double acc[1] = {0.0};
   if (!st.cg_done) {
     const float alpha = (float)st.cg_alpha, beta = (float)a.beta;
@@ -487,7 +488,6 @@ __global__ __launch_bounds__(kNT) void k_adj_update_q(AdjArgs<float> a) {
     }
   }
   store_partials<1, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_ADJ_UPD, gridDim.x);
 }
 
 // Gradients from v: dL/dy (complex64, layout of y), v as float64, and the

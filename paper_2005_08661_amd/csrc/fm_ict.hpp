@@ -277,6 +277,7 @@ __global__ __launch_bounds__(kNT) void k_ict_dots(IterArgs<T> a0, const double *
   const T *__restrict__ gg = gsrc ? gsrc : a.Gc;
   const State st = take_state<kNT, 4>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow,
                                       vw.leader);
+  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
   const int n = (int)a.geo.n;
   double acc[2] = {0.0, 0.0};
   for (int j = (int)(blockIdx.x * kNT + threadIdx.x); j < n; j += (int)(gridDim.x * kNT)) {
@@ -286,7 +287,6 @@ __global__ __launch_bounds__(kNT) void k_ict_dots(IterArgs<T> a0, const double *
     acc[1] += (double)a.Gp[j] * p;
   }
   store_partials<2, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
 }
 
 // Pivots L_jj^2 (0 outside the mask) for fm_precondition.

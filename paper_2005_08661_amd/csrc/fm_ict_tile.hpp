@@ -582,6 +582,7 @@ __global__ __launch_bounds__(kNT) void k_ict_unpack(IterArgs<T> a, IctSweep w, c
   const T *__restrict__ gg = gsrc ? gsrc : ((a.par & 1) ? a.G[1] : a.G[0]);
   const T *__restrict__ gp = (a.par & 1) ? a.G[0] : a.G[1];
   const State st = take_state<kNT, 4>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status);
+  put_state(st, a.sout, PK_DOTS, (int)gridDim.x);
   // one workgroup per kUnpackZ planes z of a tile: wave k takes columns a = k and k + 4, lane (b, z), as k_nat_unpack
   constexpr int V = 2 * kUnpackZ / 8;
   const int lb = ((int)threadIdx.x & 63) >> 3, zl = (int)threadIdx.x & 7, wv = (int)threadIdx.x / kWave;
@@ -616,7 +617,6 @@ __global__ __launch_bounds__(kNT) void k_ict_unpack(IterArgs<T> a, IctSweep w, c
     }
   }
   store_partials<2, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DOTS, (int)gridDim.x);
 }
 
 // The factor in voxel order: L [1 + n][voxels] (all of it, or the pivots L_jj^2 alone).

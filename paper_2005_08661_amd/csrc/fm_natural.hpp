@@ -213,8 +213,8 @@ __global__ __launch_bounds__(kNT) void k_nat_pack(IterArgs<T> a, Wavefront w, co
   using U = typename Bits<T>::U;
   if (blockIdx.x == 0) {  // the gradient pass's sums: no other block needs them
     const State st = take_state<kNT, 4>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status);
-    put_state(st, a.sout, PK_NONE, 0);
-    if (w.ff && threadIdx.x < 2) w.ticket[threadIdx.x] = 0u;
+  put_state(st, a.sout, PK_NONE, 0);
+      if (w.ff && threadIdx.x < 2) w.ticket[threadIdx.x] = 0u;
   }
   // one wavefront per 8 rows and column a: lane (s, b) writes the record of lane
   // (a, b) in row 8 i + s, so its loads run along z and its stores along b

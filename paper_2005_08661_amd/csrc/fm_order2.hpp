@@ -160,6 +160,7 @@ __global__ __launch_bounds__(kNT) void k_grad2(IterArgs<T> a0) {
   int base = vw.bl * chunk;
   if (base < n) load(base);
   const State st = take_state<kNT, 3>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_GRAD, vw.nb, vw.leader);
   const T alpha = (T)st.alpha;
   const T beta = (T)a.beta;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -208,7 +209,6 @@ __global__ __launch_bounds__(kNT) void k_grad2(IterArgs<T> a0) {
     if (base + stride < n) load(base + stride);
   }
   store_partials<4, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_GRAD, vw.nb, vw.leader);
 }
 
 // The iteration's gradient pass of k_grad2 with four consecutive voxels of a
@@ -264,6 +264,7 @@ __global__ __launch_bounds__(kNT) void k_grad2_q(IterArgs<float> a0) {
   int q = vw.bl * kNT + (int)threadIdx.x;
   const State st = take_state<kNT, 3>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow,
                                       vw.leader);
+  put_state(st, a.sout, PK_GRAD, vw.nb, vw.leader);
   const float alpha = (float)st.alpha;
   const float beta = (float)a.beta;
   constexpr int NP = NE * (NE - 1) / 2;
@@ -347,7 +348,6 @@ __global__ __launch_bounds__(kNT) void k_grad2_q(IterArgs<float> a0) {
     }
   }
   store_partials<4, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_GRAD, vw.nb, vw.leader);
 }
 
 // Diagonal (P = diag H with diag(C^T C) of the second-order operator) or
@@ -380,6 +380,7 @@ __global__ __launch_bounds__(kNT) void k_diag2(IterArgs<T> a0, const T *__restri
   int base = vw.bl * chunk;
   if (base < n) load(base);
   const State st = take_state<kNT, 4>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
   const double beta = a.beta;
   double acc[2] = {0.0, 0.0};
   int bad = 0;
@@ -417,7 +418,6 @@ __global__ __launch_bounds__(kNT) void k_diag2(IterArgs<T> a0, const T *__restri
   }
   if (bad) set_status(a.status, 5);
   store_partials<2, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
 }
 
 // Direction and line-search setup with the second-order regulariser (as
@@ -460,6 +460,7 @@ __global__ __launch_bounds__(kNT) void k_dir2(IterArgs<T> a0) {
   int base = vw.bl * chunk;
   if (base < n) load(base);
   const State st = take_state<kNT, 2>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_DIR, vw.nb, vw.leader);
   const T mu = (T)st.mu;
   double acc[3] = {0.0, 0.0, 0.0};
   for (; base < n; base += stride) {
@@ -488,7 +489,6 @@ __global__ __launch_bounds__(kNT) void k_dir2(IterArgs<T> a0) {
     if (base + stride < n) load(base + stride);
   }
   store_partials<3, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DIR, vw.nb, vw.leader);
 }
 
 // ---------------------------------------------------------------------------
@@ -663,6 +663,7 @@ __global__ __launch_bounds__(kNT) void k_ic3_fwd1(IterArgs<T> a0, const T *__res
   const uint8_t *__restrict__ cc = a0.ccode;
   const uint8_t *__restrict__ rd = a0.rdiag;
   const State st = take_state<kNT, 4>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_DOTS_A, vw.nb, vw.leader);
   const double beta = a.beta;
   const int first = vw.bl * kNT + (int)threadIdx.x, step = vw.nb * kNT;
   double acc[2] = {0.0, 0.0};
@@ -728,7 +729,6 @@ __global__ __launch_bounds__(kNT) void k_ic3_fwd1(IterArgs<T> a0, const T *__res
   });
   if (bad) set_status(a.status, 5);
   store_partials<2, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DOTS_A, vw.nb, vw.leader);
 }
 
 // Forward pass over colour 2 with the fill terms, its pivots, and the first
@@ -743,6 +743,7 @@ __global__ __launch_bounds__(kNT) void k_ic3_fwd2(IterArgs<T> a0, const T *__res
   const T *__restrict__ gp = a.Gp;
   const uint8_t *__restrict__ cc = a0.ccode;
   const State st = take_state<kNT, 2>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
   const double beta = a.beta;
   double acc[2] = {0.0, 0.0};
   int bad = 0;
@@ -804,7 +805,6 @@ __global__ __launch_bounds__(kNT) void k_ic3_fwd2(IterArgs<T> a0, const T *__res
   });
   if (bad) set_status(a.status, 5);
   store_partials<2, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
 }
 
 // Backward pass over colour 1: p_j = y_j / D_j - L(j+e,j) p_{j+e} - L(j-2e,j) p_{j-2e}
@@ -817,6 +817,7 @@ __global__ __launch_bounds__(kNT) void k_ic3_bwd1(IterArgs<T> a0) {
   const Cm q(g);
   const uint8_t *__restrict__ cc = a0.ccode;
   const State st = take_state<kNT, 2>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_NONE, 0, vw.leader);
   const double beta = a.beta;
   for_colour(g, q, 1, vw.bl * kNT + (int)threadIdx.x, vw.nb * kNT, [&](int t, int z0, int jv) {
     const int j = q.at(1, t);
@@ -847,7 +848,6 @@ __global__ __launch_bounds__(kNT) void k_ic3_bwd1(IterArgs<T> a0) {
     a.P[j] = pj;
     a0.Pv[jv] = pj;
   });
-  put_state(st, a.sout, PK_NONE, 0, vw.leader);
 }
 
 // Backward pass over colour 0: p_j = (g_j - sum_i H(j,i) p_i) / D_j over the
@@ -861,6 +861,7 @@ __global__ __launch_bounds__(kNT) void k_ic3_bwd0(IterArgs<T> a0, const T *__res
   const T *__restrict__ gg = gsrc ? gsrc : a.Gc;
   const uint8_t *__restrict__ cc = a0.ccode;
   const State st = take_state<kNT, 2>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_NONE, 0, vw.leader);
   const double beta = a.beta;
   for_colour(g, q, 0, vw.bl * kNT + (int)threadIdx.x, vw.nb * kNT, [&](int t, int z0, int jv) {
     const int j = q.at(0, t);
@@ -886,7 +887,6 @@ __global__ __launch_bounds__(kNT) void k_ic3_bwd0(IterArgs<T> a0, const T *__res
     a.P[j] = pj;
     a0.Pv[jv] = pj;
   });
-  put_state(st, a.sout, PK_NONE, 0, vw.leader);
 }
 
 }  // namespace fm

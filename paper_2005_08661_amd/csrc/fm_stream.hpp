@@ -164,6 +164,7 @@ __global__ __launch_bounds__(kNT) void k_grad(IterArgs<T> a0) {
   int base = vw.bl * chunk;
   if (base < n) load(base);
   const State st = take_state<kNT, 3>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_GRAD, vw.nb, vw.leader);
   const T alpha = (T)st.alpha;
   const T beta = (T)a.beta;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -209,7 +210,6 @@ __global__ __launch_bounds__(kNT) void k_grad(IterArgs<T> a0) {
     if (base + stride < n) load(base + stride);
   }
   store_partials<4, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_GRAD, vw.nb, vw.leader);
 }
 
 // ---------------------------------------------------------------------------
@@ -266,6 +266,7 @@ __global__ __launch_bounds__(kNT) void k_rb_black(IterArgs<T> a0, const T *__res
   int base = vw.bl * chunk;
   if (base < n) load(base);
   const State st = take_state<kNT, 4>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, DOTS ? PK_DOTS : PK_DOTS_A, vw.nb, vw.leader);
   const double beta = a.beta, b2 = a.beta * a.beta;
   double acc[2] = {0.0, 0.0};
   int bad = 0;
@@ -320,7 +321,6 @@ __global__ __launch_bounds__(kNT) void k_rb_black(IterArgs<T> a0, const T *__res
   }
   if (bad) set_status(a.status, 5);
   store_partials<2, kNT>(acc, a.pout);
-  put_state(st, a.sout, DOTS ? PK_DOTS : PK_DOTS_A, vw.nb, vw.leader);
 }
 
 template <typename T, bool BATCH>
@@ -352,6 +352,7 @@ __global__ __launch_bounds__(kNT) void k_rb_red(IterArgs<T> a0, const T *__restr
   int base = vw.bl * chunk;
   if (base < n) load(base);
   const State st = take_state<kNT, 2>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
   const double beta = a.beta;
   double acc[2] = {0.0, 0.0};
   int bad = 0;
@@ -378,7 +379,6 @@ __global__ __launch_bounds__(kNT) void k_rb_red(IterArgs<T> a0, const T *__restr
   }
   if (bad) set_status(a.status, 5);
   store_partials<2, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
 }
 
 // Red pass of the iteration fused with the direction step (Sec. III Algorithm,
@@ -429,6 +429,7 @@ __global__ __launch_bounds__(kNT) void k_rb_red_dir(IterArgs<T> a0) {
   int base = vw.bl * chunk;
   if (base < n) load(base);
   const State st = take_state<kNT, 2>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_DIR, vw.nb, vw.leader);
   const double beta = a.beta;
   const T mu = (T)st.mu;
   double acc[3] = {0.0, 0.0, 0.0};
@@ -471,7 +472,6 @@ __global__ __launch_bounds__(kNT) void k_rb_red_dir(IterArgs<T> a0) {
   }
   if (bad) set_status(a.status, 5);
   store_partials<3, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DIR, vw.nb, vw.leader);
 }
 
 // ---------------------------------------------------------------------------
@@ -554,6 +554,7 @@ __global__ __launch_bounds__(kNT) void k_rb_black_pair(IterArgs<T> a0) {
   int base = vw.bl * chunk;
   if (base < np) load(base);
   const State st = take_state<kNT, 4>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
   const double beta = a.beta, b2 = a.beta * a.beta;
   double acc[2] = {0.0, 0.0};
   int bad = 0;
@@ -594,7 +595,6 @@ __global__ __launch_bounds__(kNT) void k_rb_black_pair(IterArgs<T> a0) {
   }
   if (bad) set_status(a.status, 5);
   store_partials<2, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
 }
 
 template <typename T, bool BATCH>
@@ -646,6 +646,7 @@ __global__ __launch_bounds__(kNT) void k_rb_red_dir_pair(IterArgs<T> a0) {
   int base = vw.bl * chunk;
   if (base < np) load(base);
   const State st = take_state<kNT, 2>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_DIR, vw.nb, vw.leader);
   const double beta = a.beta;
   const T mu = (T)st.mu;
   double acc[3] = {0.0, 0.0, 0.0};
@@ -688,7 +689,6 @@ __global__ __launch_bounds__(kNT) void k_rb_red_dir_pair(IterArgs<T> a0) {
   }
   if (bad) set_status(a.status, 5);
   store_partials<3, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DIR, vw.nb, vw.leader);
 }
 
 // Diagonal (P = diag H) or identity preconditioner.
@@ -717,6 +717,7 @@ __global__ __launch_bounds__(kNT) void k_diag(IterArgs<T> a0, const T *__restric
   int base = vw.bl * chunk;
   if (base < n) load(base);
   const State st = take_state<kNT, 4>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
   const double beta = a.beta;
   double acc[2] = {0.0, 0.0};
   int bad = 0;
@@ -753,7 +754,6 @@ __global__ __launch_bounds__(kNT) void k_diag(IterArgs<T> a0, const T *__restric
   }
   if (bad) set_status(a.status, 5);
   store_partials<2, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
 }
 
 // ---------------------------------------------------------------------------
@@ -797,6 +797,7 @@ __global__ __launch_bounds__(kNT) void k_dir(IterArgs<T> a0) {
   int base = vw.bl * chunk;
   if (base < n) load(base);
   const State st = take_state<kNT, 2>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_DIR, vw.nb, vw.leader);
   const T mu = (T)st.mu;
   double acc[3] = {0.0, 0.0, 0.0};
   for (; base < n; base += stride) {
@@ -825,7 +826,6 @@ __global__ __launch_bounds__(kNT) void k_dir(IterArgs<T> a0) {
     if (base + stride < n) load(base + stride);
   }
   store_partials<3, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DIR, vw.nb, vw.leader);
 }
 
 // One further line-search pass (Sec. III-C eq. (ls_update)) at the current
@@ -856,6 +856,7 @@ __global__ __launch_bounds__(kNT) void k_mls(IterArgs<T> a0) {
   int base = vw.bl * chunk;
   if (base < n) load(base);
   const State st = take_state<kNT, 3>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow, vw.leader);
+  put_state(st, a.sout, PK_MLS, vw.nb, vw.leader);
   const T alpha = (T)st.alpha;
   double acc[2] = {0.0, 0.0};
   for (; base < n; base += stride) {
@@ -871,7 +872,6 @@ __global__ __launch_bounds__(kNT) void k_mls(IterArgs<T> a0) {
     if (base + stride < n) load(base + stride);
   }
   store_partials<2, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_MLS, vw.nb, vw.leader);
 }
 
 // Mark loaded values as used where they were loaded: the compiler would
@@ -924,6 +924,7 @@ __global__ __launch_bounds__(kNT) void k_mls_q(IterArgs<float> a0) {
   int q = vw.bl * kNT + (int)threadIdx.x;
   const State st = take_state<kNT, 3>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow,
                                       vw.leader);
+  put_state(st, a.sout, PK_MLS, vw.nb, vw.leader);
   const float alpha = (float)st.alpha;
   constexpr int NP = NE * (NE - 1) / 2;
   PairC<float> pc[NP];  // the echo-pair constants, read once into scalar registers
@@ -958,7 +959,6 @@ __global__ __launch_bounds__(kNT) void k_mls_q(IterArgs<float> a0) {
     }
   }
   store_partials<2, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_MLS, vw.nb, vw.leader);
 }
 
 // The gradient pass of k_grad (iteration only: no final pass, no user
@@ -1008,6 +1008,7 @@ __global__ __launch_bounds__(kNT) void k_grad_q(IterArgs<float> a0) {
   int q = vw.bl * kNT + (int)threadIdx.x;
   const State st = take_state<kNT, 3>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow,
                                       vw.leader);
+  put_state(st, a.sout, PK_GRAD, vw.nb, vw.leader);
   const float alpha = (float)st.alpha;
   const float beta = (float)a.beta;
   constexpr int NP = NE * (NE - 1) / 2;
@@ -1091,7 +1092,6 @@ __global__ __launch_bounds__(kNT) void k_grad_q(IterArgs<float> a0) {
     }
   }
   store_partials<4, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_GRAD, vw.nb, vw.leader);
 }
 
 }  // namespace fm

@@ -169,6 +169,7 @@ __global__ __launch_bounds__(kNT) void k_rb_black_tile(IterArgs<T> a0, TileShape
   for (int d = 0; d < kTileDepth; ++d) hq[d] = tile_b_halo(a, g, t.x0 + d, t.hy, t.hz, t.hok && t.x0 + d < t.x1);
   const State st = take_state<kNT, 4>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow,
                                       vw.leader);
+  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
   const double beta = a.beta, b2 = a.beta * a.beta;
   double acc[2] = {0.0, 0.0};
   int bad = 0;
@@ -252,7 +253,6 @@ __global__ __launch_bounds__(kNT) void k_rb_black_tile(IterArgs<T> a0, TileShape
   }
   if (bad) set_status(a.status, 5);
   store_partials<2, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DOTS, vw.nb, vw.leader);
 }
 
 // ---------------------------------------------------------------------------
@@ -332,6 +332,7 @@ __global__ __launch_bounds__(kNT) void k_rb_red_dir_tile(IterArgs<T> a0, TileSha
   for (int d = 0; d < kTileDepth; ++d) hq[d] = tile_r_halo(a, g, t.x0 + d, t.hy, t.hz, t.hok && t.x0 + d < t.x1);
   const State st = take_state<kNT, 2>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status, vw.prow,
                                       vw.leader);
+  put_state(st, a.sout, PK_DIR, vw.nb, vw.leader);
   const double beta = a.beta;
   const T mu = (T)st.mu;
   double acc[3] = {0.0, 0.0, 0.0};
@@ -413,7 +414,6 @@ __global__ __launch_bounds__(kNT) void k_rb_red_dir_tile(IterArgs<T> a0, TileSha
   }
   if (bad) set_status(a.status, 5);
   store_partials<3, kNT>(acc, a.pout);
-  put_state(st, a.sout, PK_DIR, vw.nb, vw.leader);
 }
 
 }  // namespace fm
