@@ -64,6 +64,7 @@ struct fm_plan {
   int npairs = 0;
   int grid = 1;   // blocks of the kBlock-thread kernels
   int sgrid = 1;  // blocks of the streaming iteration passes (kNT threads)
+  bool few = false;  // few enough voxels for a thread each
   size_t tsize = 8;  // bytes of the working type
   // device workspace
   void *dat = nullptr;
@@ -534,14 +535,13 @@ bool fused_red_dir(const fm_plan *p) {
 // Values per partial block left by the last pass of an iteration.
 int tail_nvals(const fm_plan *p) { return p->prm.nmls > 1 ? 2 : 3; }
 
-#ifndef FM_TILE_XCMIN
-#define FM_TILE_XCMIN 4
-#endif
 
 // Plane-march shape of the tiled red-black passes: strips of ty columns (all
-// pair slots of a workgroup on one plane), runs of at least FM_TILE_XCMIN
-// planes, lengthened until the grid fits the partial-sum rows.  grid 0 where
-// the tile does not apply (odd or long columns).
+// pair slots of a workgroup on one plane), runs of 4 planes, of fewer where
+// that leaves compute units without a workgroup (a run is a serial chain; with
+// 512 workgroups aimed at instead of 256, 91x109x91 F64 took 3.35 ms, not 3.19),
+// lengthened until the grid fits the partial-sum rows.  grid 0 where the tile
+// does not apply (odd or long columns).
 fm::TileShape tile_shape(const fm::Geo &g) {
   fm::TileShape t{};
   if (g.nz % 2 != 0 || g.nz > fm::kTileMaxNz) return t;
@@ -549,7 +549,8 @@ fm::TileShape tile_shape(const fm::Geo &g) {
   t.ty = std::min(fm::kTileSlots / nzp, g.ny);
   t.nyt = (g.ny + t.ty - 1) / t.ty;
   if (t.nyt > kMaxGrid) return fm::TileShape{};
-  t.xc = std::max<int>(FM_TILE_XCMIN, (int)(((int64_t)t.nyt * g.nx + kMaxGrid - 1) / kMaxGrid));
+  const int64_t planes = (int64_t)t.nyt * g.nx;  // over all strips
+  t.xc = std::max<int>((int)std::clamp<int64_t>(planes / 256, 1, 4), (int)((planes + kMaxGrid - 1) / kMaxGrid));
   while ((int64_t)t.nyt * ((g.nx + t.xc - 1) / t.xc) > kMaxGrid) ++t.xc;
   t.grid = t.nyt * ((g.nx + t.xc - 1) / t.xc);
   return t;
@@ -568,9 +569,9 @@ int tail_nparts(const fm_plan *p) {
 // iteration's gradient pass (or by the final pass).
 template <typename T, int LMAX>
 fm_status enqueue_iteration(fm_plan *p, hipStream_t s, Recorder *rec = nullptr) {
-  // FP32, 2-6 echoes, columns a multiple of 4: the 16-byte-load passes (gradient
+  // FP32, 2-6 echoes, columns a multiple of 4, not a thread per voxel: the 16-byte-load passes (gradient
   // passes of either stencil; the line-search passes have none)
-  const int quad = std::is_same<T, float>::value && p->prm.necho <= 6 && p->geo.nz % 4 == 0 ? p->prm.necho : 0;
+  const int quad = std::is_same<T, float>::value && p->prm.necho <= 6 && p->geo.nz % 4 == 0 && !p->few ? p->prm.necho : 0;
   if (p->reg2) {
     if (quad == 2)
       FM_LAUNCH(FM_K_GRAD, (fm::k_grad2_q<2>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
@@ -595,7 +596,11 @@ fm_status enqueue_iteration(fm_plan *p, hipStream_t s, Recorder *rec = nullptr) 
   } else if (quad == 6) {
     FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<6, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
   } else {
-    FM_LAUNCH(FM_K_GRAD, (fm::k_grad<T, LMAX, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
+    if (p->few)
+      FM_LAUNCH(FM_K_GRAD, (fm::k_grad<T, LMAX, false, 1>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
+    else
+      FM_LAUNCH(FM_K_GRAD, (fm::k_grad<T, LMAX, false, fm::kVGrad<T>>), dim3(p->sgrid), dim3(fm::kNT), s,
+                iter_args<T>(p, p->q++));
   }
   FM_LAUNCH_CHECK();
   set_parts(p, p->sgrid, 4);
@@ -634,7 +639,10 @@ fm_status enqueue_iteration(fm_plan *p, hipStream_t s, Recorder *rec = nullptr) 
     } else if (p->reg2) {
       FM_LAUNCH(FM_K_DIR, (fm::k_dir2<T>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
     } else {
-      FM_LAUNCH(FM_K_DIR, (fm::k_dir<T, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
+      if (p->few)
+        FM_LAUNCH(FM_K_DIR, (fm::k_dir<T, false, 1>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
+      else
+        FM_LAUNCH(FM_K_DIR, (fm::k_dir<T, false, fm::Vpt<T>::v>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
     }
     FM_LAUNCH_CHECK();
   }
@@ -651,7 +659,11 @@ fm_status enqueue_iteration(fm_plan *p, hipStream_t s, Recorder *rec = nullptr) 
     } else if (quad == 6) {
       FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<6, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
     } else {
-      FM_LAUNCH(FM_K_MLS, (fm::k_mls<T, LMAX, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
+      if (p->few)
+        FM_LAUNCH(FM_K_MLS, (fm::k_mls<T, LMAX, false, 1>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
+      else
+        FM_LAUNCH(FM_K_MLS, (fm::k_mls<T, LMAX, false, fm::kVMls<T, LMAX>>), dim3(p->sgrid), dim3(fm::kNT), s,
+                  iter_args<T>(p, p->q++));
     }
     FM_LAUNCH_CHECK();
     set_parts(p, p->sgrid, 2);
@@ -669,7 +681,7 @@ fm_status enqueue_final(fm_plan *p, double *f_out, hipStream_t s) {
   if (p->reg2)
     hipLaunchKernelGGL((fm::k_grad2<T, LMAX>), dim3(p->sgrid), dim3(fm::kNT), 0, s, a);
   else
-    hipLaunchKernelGGL((fm::k_grad<T, LMAX, false>), dim3(p->sgrid), dim3(fm::kNT), 0, s, a);
+    hipLaunchKernelGGL((fm::k_grad<T, LMAX, false, fm::kVGrad<T>>), dim3(p->sgrid), dim3(fm::kNT), 0, s, a);
   FM_LAUNCH_CHECK();
   set_parts(p, p->sgrid, 4);
   const uint64_t q = p->q++;
@@ -1016,8 +1028,26 @@ void plan_geometry(fm_plan *p, int32_t nz) {
   p->pad = (((p->reg2 ? 2 : 1) * p->geo.sx + 63) / 64) * 64;
 }
 
+// Volumes with no more voxels than threads in the largest grid (FP32, where four voxels a thread
+// pay from less on: half as many) give each voxel a thread of its own: a pass of such a volume lasts as long as one thread's chain, and two or four
+// voxels in it lengthen the chain while most of the chip idles (74x74x10 MIX 1.73 -> 1.36 ms
+// together with the tile passes' shorter runs, 51x66x15 1.35 -> 1.23, 32x32x16 F64 natural
+// 3.87 -> 3.70; 149x148x11 MIX, beyond the line: 1.89 ms, 1.80 in fours).  Second-order volumes that take the four-voxel passes stay with them and
+// their grid (49x52x52: 2.18 ms, 2.28 with a thread per voxel).
+bool few_voxels(const fm_params &q) {
+  const int64_t most = (int64_t)kMaxGrid * fm::kNT / (q.precision == FM_PREC_MIX ? 2 : 1);
+  return (int64_t)q.nx * q.ny * q.nz <= most &&
+         !(q.reg_order == 2 && q.precision == FM_PREC_MIX && q.necho <= 6 && q.nz % 4 == 0);
+}
+
+// Workgroups of the streaming iteration passes.
+int stream_grid(const fm_plan *p) {
+  const int64_t v = p->few ? 1 : p->mix ? fm::Vpt<float>::v : fm::Vpt<double>::v, chunk = fm::kNT * v;
+  return (int)std::max<int64_t>(1, std::min<int64_t>((p->n + chunk - 1) / chunk, kMaxGrid));
+}
+
 // Column length of the plan's arrays.  The pair and tile passes of red-black IC(0) need an even
-// one, the 16-byte-load passes (FP32, up to 6 echoes) a multiple of 4; a column is lengthened to
+// one, the 16-byte-load passes (FP32, up to 6 echoes, more voxels than threads) a multiple of 4; a column is lengthened to
 // it with voxels outside the mask where that adds at most an eighth (beyond, the added bytes
 // cost more than the per-voxel passes: 10 -> 12 would add a fifth).  91x109x91, F64, 40
 // iterations: 3.97 -> 3.61 ms; drawn odd sizes 3.31 -> 2.59 and 2.91 -> 2.39 ms.  Plans that
@@ -1030,7 +1060,7 @@ int32_t padded_columns(const fm_plan *p) {
   const bool none = q.precond == FM_PRECOND_DIAG || q.precond == FM_PRECOND_NONE;
   if (p->reg2 || p->res_ok || !(rb || none) || p->n > ((int64_t)1 << 26)) return q.nz;
   const int32_t up4 = (q.nz + 3) / 4 * 4, up2 = (q.nz + 1) / 2 * 2;
-  if (p->mix && q.necho <= 6 && 8 * (up4 - q.nz) <= q.nz) return up4;
+  if (p->mix && q.necho <= 6 && !p->few && 8 * (up4 - q.nz) <= q.nz) return up4;
   if (rb && 8 * (up2 - q.nz) <= q.nz) return up2;
   return q.nz;
 }
@@ -1385,6 +1415,7 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
   p->mix = prm->precision == FM_PREC_MIX;
   p->tsize = p->mix ? sizeof(float) : sizeof(double);
   p->reg2 = prm->reg_order == 2;
+  p->few = few_voxels(*prm);
   if (hipGetDevice(&p->device) != hipSuccess) {
     delete p;
     return fail(FM_ERR_HIP, "hipGetDevice failed");
@@ -1407,10 +1438,7 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
   const int64_t blocks = (p->n + kBlock - 1) / kBlock;
   p->grid = (int)(blocks < kMaxGrid ? blocks : kMaxGrid);
   if (p->grid < 1) p->grid = 1;
-  const int64_t chunk = (int64_t)fm::kNT * (p->mix ? fm::Vpt<float>::v : fm::Vpt<double>::v);
-  const int64_t sblocks = (p->n + chunk - 1) / chunk;
-  p->sgrid = (int)(sblocks < kMaxGrid ? sblocks : kMaxGrid);
-  if (p->sgrid < 1) p->sgrid = 1;
+  p->sgrid = stream_grid(p);
   auto cleanup = [&](fm_status st) {
     free_plan(p);
     return st;

@@ -43,6 +43,10 @@ template <typename T, int V32>
 struct Vk {
   static constexpr int v = sizeof(T) == 4 ? V32 : FM_VPT64;
 };
+template <typename T>
+constexpr int kVGrad = Vk<T, FM_V_GRAD>::v;
+template <typename T, int LMAX>
+constexpr int kVMls = Vk<T, LMAX <= 4 ? FM_V_MLS : FM_VPT32>::v;
 
 // Every array read at neighbour offsets is padded by one x-plane (sx
 // elements) on both sides, so j + off is always a valid address; the code
@@ -131,9 +135,8 @@ __device__ __forceinline__ VArgs<T> at_volume(const IterArgs<T> &a0, const VolVi
 //   g_j = dphi_j(f_j) + beta (C^T C f)_j,  D_j = Huber curvature (eq. (ls_huber)),
 // hinv_j = 1 / (D_j + beta deg_j) for the red-black preconditioner.
 // Partial sums: sum phi, f^T C^T C f, ||g||^2, z_prev^T g.
-template <typename T, int LMAX, bool BATCH>
+template <typename T, int LMAX, bool BATCH, int V>
 __global__ __launch_bounds__(kNT) void k_grad(IterArgs<T> a0) {
-  constexpr int V = Vk<T, FM_V_GRAD>::v;
   const VolView vw = vol_view<BATCH>(a0);
   const VArgs<T> a = at_volume<BATCH>(a0, vw);
   const Geo g = a.geo;
@@ -762,9 +765,8 @@ __global__ __launch_bounds__(kNT) void k_diag(IterArgs<T> a0, const T *__restric
 // z = -p + mu z_prev, A = z^T C^T C f, B = ||C z||^2 (once per outer
 // iteration) and d0 = sum z^2 D, from which the next kernel takes the first
 // step alpha = -z^T g / (d0 + beta B).
-template <typename T, bool BATCH>
+template <typename T, bool BATCH, int V>
 __global__ __launch_bounds__(kNT) void k_dir(IterArgs<T> a0) {
-  constexpr int V = Vpt<T>::v;
   const VolView vw = vol_view<BATCH>(a0);
   const VArgs<T> a = at_volume<BATCH>(a0, vw);
   const Geo g = a.geo;
@@ -831,9 +833,8 @@ __global__ __launch_bounds__(kNT) void k_dir(IterArgs<T> a0) {
 // One further line-search pass (Sec. III-C eq. (ls_update)) at the current
 // alpha: S1 = z^T grad Phi(f + alpha z), S2 = sum z^2 d(f + alpha z); the next
 // kernel applies alpha <- alpha - (S1 + beta A + alpha beta B) / (S2 + beta B).
-template <typename T, int LMAX, bool BATCH>
+template <typename T, int LMAX, bool BATCH, int V>
 __global__ __launch_bounds__(kNT) void k_mls(IterArgs<T> a0) {
-  constexpr int V = Vk<T, LMAX <= 4 ? FM_V_MLS : FM_VPT32>::v;
   const VolView vw = vol_view<BATCH>(a0);
   const VArgs<T> a = at_volume<BATCH>(a0, vw);
   const Geo g = a.geo;
