@@ -572,6 +572,8 @@ fm_status enqueue_iteration(fm_plan *p, hipStream_t s, Recorder *rec = nullptr) 
   // FP32, 2-6 echoes, columns a multiple of 4, not a thread per voxel: the 16-byte-load passes (gradient
   // passes of either stencil; the line-search passes have none)
   const int quad = std::is_same<T, float>::value && p->prm.necho <= 6 && p->geo.nz % 4 == 0 && !p->few ? p->prm.necho : 0;
+  // two fours or more per thread (at five and six echoes the registers are too many)
+  const bool early = p->n >= (int64_t)8 * kMaxGrid * fm::kNT;
   if (p->reg2) {
     if (quad == 2)
       FM_LAUNCH(FM_K_GRAD, (fm::k_grad2_q<2>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
@@ -586,11 +588,20 @@ fm_status enqueue_iteration(fm_plan *p, hipStream_t s, Recorder *rec = nullptr) 
     else
       FM_LAUNCH(FM_K_GRAD, (fm::k_grad2<T, LMAX>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
   } else if (quad == 2) {
-    FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<2, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+    if (early)
+      FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<2, false, true>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+    else
+      FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<2, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
   } else if (quad == 3) {
-    FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<3, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+    if (early)
+      FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<3, false, true>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+    else
+      FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<3, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
   } else if (quad == 4) {
-    FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<4, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+    if (early)
+      FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<4, false, true>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+    else
+      FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<4, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
   } else if (quad == 5) {
     FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<5, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
   } else if (quad == 6) {
@@ -649,11 +660,20 @@ fm_status enqueue_iteration(fm_plan *p, hipStream_t s, Recorder *rec = nullptr) 
   set_parts(p, dir_parts, 3);
   for (int k = 1; k < p->prm.nmls; ++k) {
     if (quad == 2) {
-      FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<2, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+      if (early)
+        FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<2, false, true>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+      else
+        FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<2, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
     } else if (quad == 3) {
-      FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<3, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+      if (early)
+        FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<3, false, true>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+      else
+        FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<3, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
     } else if (quad == 4) {
-      FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<4, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+      if (early)
+        FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<4, false, true>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+      else
+        FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<4, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
     } else if (quad == 5) {
       FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<5, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
     } else if (quad == 6) {

@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LMAX <= 
     const int32_t yy = (int32_t)((j / g.nz) % g.ny);
     const int32_t x = (int32_t)(j / g.sx);
     const bool own = z < g.uz;  // the caller's arrays hold this voxel
-    const int64_t col = (int64_t)x * g.ny + yy, ju = col * g.uz + (own ? z : 0), sxu = g.user_sx(), nu = g.user_n();
+    const int64_t ju = g.uz == g.nz ? j : ((int64_t)x * g.ny + yy) * g.uz + (own ? z : 0), sxu = g.user_sx(), nu = g.user_n();
     const bool in = own && a.mask[ju] != 0;
     uint32_t c = 0;
     if (in) {
