@@ -250,7 +250,7 @@ __global__ __launch_bounds__(kNT) void k_adj_black_pair(AdjArgs<T> a) {
   int q = (int)blockIdx.x * kNT + (int)threadIdx.x;
   if (q < np) load(q);
   const State st = take_state<kNT, 1>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, nullptr, a.status);
-  put_state(st, a.sout, PK_ADJ_RHO, gridDim.x);
+  put_state(st, a.sout, PK_DOTS_A, gridDim.x);
   const double beta = a.beta, b2 = a.beta * a.beta;
   double acc[1] = {0.0};
   int bad = 0;
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(kNT) void k_adj_red_dir_pair(AdjArgs<T> a) {
   double acc[1] = {0.0};
   int bad = 0;
   if (!st.cg_done) {
-    const double rho = st.gtp, beta = a.beta;
+    const double rho = st.acc0, beta = a.beta;  // (left as the first of two sums)
     const T bcg = (T)((st.cg_it > 0 && st.cg_rho_prev != 0.0) ? rho / st.cg_rho_prev : 0.0);
     st.cg_rho = rho;
     for (; q < np; q += stride) {

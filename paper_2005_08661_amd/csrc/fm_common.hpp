@@ -38,7 +38,6 @@ enum PartKind : int32_t {
   PK_ADJ_CURV = 8, // adjoint CG: d^T H d
   PK_ADJ_UPD = 9,  // adjoint CG: ||r||^2 after the update
   PK_ADJ_FIN = 10, // adjoint: v^T C^T C fhat
-  PK_ADJ_RHO = 11, // adjoint CG: r^T M^{-1} r
 };
 
 // Scalar state of one solve.  Two copies ping-pong along the kernel chain:
@@ -418,10 +417,6 @@ __device__ __forceinline__ void consume(State &s, const double (&t)[kMaxK], doub
           s.cg_done = 1;
         }
       }
-      break;
-    }
-    case PK_ADJ_RHO: {
-      s.gtp = t[0];
       break;
     }
     case PK_ADJ_CURV: {
