@@ -1436,15 +1436,7 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
   p->tsize = p->mix ? sizeof(float) : sizeof(double);
   p->reg2 = prm->reg_order == 2;
   p->few = few_voxels(*prm);
-  if (hipGetDevice(&p->device) != hipSuccess) {
-    delete p;
-    return fail(FM_ERR_HIP, "hipGetDevice failed");
-  }
   plan_geometry(p, prm->nz);
-  p->res_ok = plan_resident(p);
-  const int32_t nzp = padded_columns(p);
-  plan_geometry(p, nzp);
-  if (nzp != prm->nz && p->n + 2 * p->pad >= ((int64_t)1 << 31)) plan_geometry(p, prm->nz);
   p->cm = p->reg2 && prm->precond == FM_PRECOND_IC0;
   if (p->cm) {
     const int64_t m = ((int64_t)prm->nz + 2) / 3;
@@ -1454,6 +1446,12 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
     delete p;
     return fail(FM_ERR_SHAPE, "volume too large for 32-bit voxel indices");
   }
+  if (hipGetDevice(&p->device) != hipSuccess) {
+    delete p;
+    return fail(FM_ERR_HIP, "hipGetDevice failed");
+  }
+  p->res_ok = plan_resident(p);
+  plan_geometry(p, padded_columns(p));  // (at most 9/8 of 2^26 voxels: no index bound to check again)
   p->lmax = prm->necho <= 4 ? 4 : (prm->necho <= 8 ? 8 : 16);
   const int64_t blocks = (p->n + kBlock - 1) / kBlock;
   p->grid = (int)(blocks < kMaxGrid ? blocks : kMaxGrid);
