@@ -19,15 +19,19 @@
 // Values of other lanes come from a ring of the last steps in LDS, one column of
 // positions wider than the tile on its -x and -y sides, where the faces of the
 // neighbour tiles are written as they arrive.  A position without a voxel holds
-// what leaves every sum as it is: L_kk = 1, no entries, y = 0 and an infinite drop
-// threshold, by which a row drops its entry there; a lane without a voxel has
-// beta = 0 and so forms no entries.  No masks, as there.
+// what leaves every sum as it is: L_kk = 1, no entries, y = p = 0 and an infinite
+// drop threshold, by which a row drops its entry there (a NaN is dropped too).  A
+// lane without a voxel selects y and p (not products with zero: a NaN or an infinity
+// must not cross the mask); it knows itself by the sign of its -beta, which is +0,
+// and backward by 1/L_jj = 0.  No masks, as there.
 //
 // The arithmetic is that of fm_ict.hpp, each product rounded before it is
 // subtracted.  Quotients are formed from the reciprocal of L_kk that its row
 // leaves, with the remainder's correction that makes them the correctly rounded
 // ones (Markstein, Computation of elementary functions on the IBM RISC System/6000
 // processor, IBM J. Res. Dev. 34, 1990), in 3 operations instead of a division.
+// An infinite L_kk stands as the largest finite number with the reciprocal 0, by
+// which every quotient is 0; y and p take an infinite numerator through v_div_fixup.
 //
 // Measured at 128x128x64 (MIX, level 1): forward 3.0 ms -> 500 us, backward 2.8 ms
 // -> 323 us a sweep, k_ict_pack 20 us and k_ict_unpack 15 us on top.  A step takes
@@ -44,6 +48,7 @@ namespace fm {
 
 constexpr int kIctU = 4;      // steps per group: two register sets of face values, and a ring of 8 steps in LDS
 constexpr int kIctRing = 8;
+constexpr double kIctInf = 0x1.fffffffffffffp+1023;  // an infinite L_jj (a finite one is below 2^512)
 constexpr int kIctPos = 81;   // ring positions of a step: (a + 1) * 9 + b + 1 of the 8x8 columns and their halo
 
 // Offset u of the pattern in the sheared coordinates, and the steps back to it.
@@ -146,7 +151,7 @@ __global__ __launch_bounds__(kNT) void k_ict_pack(Geo g, double beta, double fac
     const int la = i / nb, S = (i - la * nb) * 8 + (lane >> 3);
     const int tx = tile / w.nty, ty = tile - tx * w.nty;
     const int x = tx * kTile + la, y = ty * kTile + lb - C::K * la, z = S - la - (C::K + 1) * lb;
-    double h = 1.0, t = __builtin_inf(), gv = 0.0, nbeta = 0.0;
+    double h = 1.0, t = __builtin_inf(), gv = 0.0, nbeta = 0.0;  // (a voxel's nbeta is negative, or -0)
     if (x < g.nx && y >= 0 && y < g.ny && z >= 0 && z < g.nz) {
       const int64_t j = ((int64_t)x * g.ny + y) * g.nz + z;
       const uint32_t c = code[j];
@@ -157,7 +162,8 @@ __global__ __launch_bounds__(kNT) void k_ict_pack(Geo g, double beta, double fac
         if (c & NB_XP) cn = cn + beta;
         if (c & NB_YP) cn = cn + beta;
         if (c & NB_ZP) cn = cn + beta;
-        t = plain_nan(tol * cn);
+        t = tol * cn;
+        t = t == t ? t : 0.0;  // factor 0 and an infinite H_max: every entry is kept
         gv = plain_nan((double)gj);
         nbeta = -beta;
       }
@@ -177,6 +183,11 @@ __global__ __launch_bounds__(kNT) void k_ict_pack(Geo g, double beta, double fac
 __device__ __forceinline__ double quotient(double s, double b, double y) {
   const double q = s * y;
   return fma(fma(-b, q, s), y, q);
+}
+
+// The same where s may be infinite or NaN.
+__device__ __forceinline__ double quotient_any(double s, double b, double y) {
+  return __builtin_amdgcn_div_fixup(quotient(s, b, y), b, s);
 }
 
 // One face's values of a group of kIctU steps: R records each, S slots a step,
@@ -352,6 +363,7 @@ __global__ __launch_bounds__(64) void k_ict_fwd_wave(IctSweep w, int32_t *status
       if (S > 0) store(v, vo, k);
       __builtin_amdgcn_sched_barrier(0);
       const double h = rec_d(s.h[k]), t = rec_d2(s.h[k]), gj = rec_d(s.g[k]), nbeta = rec_d2(s.g[k]);
+      const bool voxel = (int32_t)s.g[k][3] < 0;
       double row[NO];
 #pragma unroll
       for (int u = 0; u < NO; ++u) {
@@ -360,7 +372,7 @@ __global__ __launch_bounds__(64) void k_ict_fwd_wave(IctSweep w, int32_t *status
         for (int e = 0; e < u; ++e)
           if (ict_pair<LEVEL>(u, e) >= 0) sum = sum - row[e] * lkm[u][e];
         const double val = quotient(sum, lkk[u], rkk[u]);
-        row[u] = fabs(val) < tk[u] ? 0.0 : val;
+        row[u] = fabs(val) >= tk[u] ? val : 0.0;
       }
       double diag = h;
 #pragma unroll
@@ -384,9 +396,10 @@ __global__ __launch_bounds__(64) void k_ict_fwd_wave(IctSweep w, int32_t *status
       double yv = gj;
 #pragma unroll
       for (int u = 0; u < NO; ++u) yv = yv - row[u] * yk[u];
-      p_l = good ? l : 0.0;
-      p_r = good ? r : 0.0;
-      p_y = quotient(yv, p_l, p_r);
+      p_l = good ? fmin(l, kIctInf) : 0.0;  // (l is NaN for an infinite diag)
+      const bool live = voxel && good && fin;
+      p_r = live ? r : 0.0;
+      p_y = live ? quotient_any(yv, l, r) : 0.0;
       p_t = t;
 #pragma unroll
       for (int u = 0; u < NO; ++u) p_row[u] = row[u];
@@ -532,7 +545,8 @@ __global__ __launch_bounds__(64) void k_ict_bwd_wave(IctSweep w, int32_t *status
       double sum = p_y - own;
 #pragma unroll
       for (int u = NF - 1; u >= 0; --u) sum = sum - o[u];
-      p = quotient(sum, rec_d(s.l[k]), rec_d2(s.l[k]));
+      const double pj = quotient_any(sum, rec_d(s.l[k]), rec_d2(s.l[k]));
+      p = rec_d2(s.l[k]) != 0.0 ? pj : 0.0;
 #pragma unroll
       for (int u = 0; u < NF; ++u) c[u] = (u & 1 ? rec_d2(s.e[k][u / 2]) : rec_d(s.e[k][u / 2])) * p;
       own = (NF & 1 ? rec_d2(s.e[k][NF / 2]) : rec_d(s.e[k][NF / 2])) * p;
@@ -628,7 +642,7 @@ __global__ __launch_bounds__(kBlock) void k_ict_factor(Geo g, const uint8_t *__r
     const int z = (int)(j % g.nz), y = (int)(j / g.nz % g.ny), x = (int)(j / g.sx);
     const bool in = code[j] & NB_SELF;
     const Rec *r = w.rec + ict_place<LEVEL>(w, x, y, z);
-    const double l = in ? rec_d(r[0]) : 0.0;
+    const double lj = in ? rec_d(r[0]) : 0.0, l = lj == kIctInf ? __builtin_inf() : lj;
     if (piv) piv[j] = l * l;
     if (!L) continue;
     L[j] = l;

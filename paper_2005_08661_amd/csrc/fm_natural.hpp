@@ -17,7 +17,8 @@
 //   beforehand as [tile][step][lane], so a step's loads and stores are one
 //   contiguous run per wavefront at uniform offsets, and gives every lane
 //   without a voxel (outside the column, the volume or the mask) h = +inf and
-//   g = 0, for which the recurrences yield 1/P = 0 and x = p = 0: no masks, no
+//   g = 0, for which the step selects 1/P = 0 and x = p = 0 (selects, not products
+//   with zero: a NaN or an infinity must not cross the mask): no masks, no
 //   branches, no address arithmetic.  The forward sweep overwrites h by 1/P and g
 //   by x in place; k_nat_unpack brings p back to voxel order and takes the
 //   dot products.
@@ -31,9 +32,10 @@
 //   group before; the records it takes per step (one load, two stores) stay
 //   below the 64 memory operations a wave may have in flight.
 //
-// Measured at 128x128x64 (MIX), per launch: forward 598 -> 105 us, backward
-// 550 -> 89 us, k_nat_pack 12 and k_nat_unpack 13 us on top; a step takes 0.105
-// and 0.06 us (0.7 us before), a hop about 3 us (21 us before).  Groups of 4
+// Measured at 128x128x64 (MIX), per launch: forward 598 -> 104 us, backward
+// 550 -> 92 us (89 us without the select of p, which lengthens the chain), k_nat_pack
+// 12 and k_nat_unpack 13 us on top; a step takes 0.105 and 0.06 us (0.7 us before), a
+// hop about 3 us (21 us before).  Groups of 4
 // steps shorten a hop and lengthen every step (a group's loads take 1.7 us to
 // arrive): 117 against 109 us forward.
 //
@@ -317,6 +319,7 @@ template <typename T, bool BLOCK = false>
 struct FwdLane {
   double r = 0.0;  // 1/P of the previous row (this column's -z neighbour)
   T x = T(0);      // x of the row before that
+  bool own = false;  // the previous row's h is finite (it has a voxel)
   bool bad = false;
   __device__ __forceinline__ Rec step(bool fx, bool fy, int xsrc, const Rec &fxr, const Rec &fyr, const Rec &in,
                                       double beta, double b2) {
@@ -366,11 +369,12 @@ struct FwdLane {
     const double x4 = x3 * r;
     FM_STAGE;
     q = fma(q, e, q);
-    x = (T)x4;
+    x = own ? (T)x4 : T(0);
     FM_STAGE;
     e = fma(-piv, q, 1.0);
     q = fma(q, e, q);
     r = pos && fin ? q : 0.0;
+    own = fin;
     return make_rec(r, x);
   }
 };
@@ -394,7 +398,8 @@ struct BwdLane {
       py = (double)(fy ? fyp : pyl);
       px = (double)(fx ? fxp : pxl);
     }
-    p = (T)fma(beta * (((double)p + py) + px), rec_d(in), (double)x_next);
+    const T pj = (T)fma(beta * (((double)p + py) + px), rec_d(in), (double)x_next);
+    p = rec_d(in) != 0.0 ? pj : T(0);
     x_next = rec_t(in, T());
     return p;
   }
