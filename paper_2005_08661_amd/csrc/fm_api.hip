@@ -837,8 +837,8 @@ bool sweeps_in_tiles(const fm_plan *p) {
 }
 
 // Face buffers and tickets of the natural-order sweeps: rows past a sweep and
-// the last tile (no neighbour) stay 0.
-fm_status alloc_faces(fm_plan *p) {
+// the last tile (no neighbour) stay 0.  Cleared on the stream whose sweeps come first.
+fm_status alloc_faces(fm_plan *p, hipStream_t s) {
   fm::Wavefront &w = p->wf;
   w.frow = w.nrow + fm::kNatU + fm::kTile - 1;
   const size_t faces = ((size_t)w.ntiles + 1) * w.frow * fm::kFaceSlots;
@@ -846,7 +846,8 @@ fm_status alloc_faces(fm_plan *p) {
   if (!plan_alloc(p, &ff, sizeof(fm::Rec) * faces) || !plan_alloc(p, &fp, p->tsize * faces) ||
       !plan_alloc(p, &tk, sizeof(uint32_t) * 2))
     return fail(FM_ERR_ALLOC, "hipMalloc of the face buffers failed");
-  if (hipMemset(ff, 0, sizeof(fm::Rec) * faces) != hipSuccess || hipMemset(fp, 0, p->tsize * faces) != hipSuccess)
+  if (hipMemsetAsync(ff, 0, sizeof(fm::Rec) * faces, s) != hipSuccess ||
+      hipMemsetAsync(fp, 0, p->tsize * faces, s) != hipSuccess)
     return fail(FM_ERR_HIP, "hipMemset of the face buffers failed");
   w.ff = (fm::Rec *)ff;
   w.fp = fp;
@@ -1164,8 +1165,10 @@ fm_status read_status(fm_plan *p, hipStream_t s, int32_t *status) {
 
 // ---------------------------------------------------------------------------
 // Implicit adjoint: CG on the exact Hessian at fhat, preconditioned like the
-// iteration.  The chain has its own state/partial ping-pong (position aq).
-fm_status adj_alloc(fm_plan *p) {
+// iteration.  The chain has its own state/partial ping-pong (position aq).  The
+// workspace is cleared on the call's stream s, which a memset on the default stream
+// need not precede.
+fm_status adj_alloc(fm_plan *p, hipStream_t s) {
   if (p->adj_ready) return FM_OK;
   const size_t n = (size_t)p->n, ts = p->tsize;
   bool ok = plan_alloc_padded(p, &p->aR, n, ts) && plan_alloc_padded(p, &p->aZ, n, ts) &&
@@ -1177,11 +1180,11 @@ fm_status adj_alloc(fm_plan *p) {
             plan_alloc(p, (void **)&p->a_part, sizeof(double) * 2 * p->part_rows * kMaxK) &&
             plan_alloc(p, (void **)&p->aS, sizeof(fm::State) * 2) && plan_alloc(p, (void **)&p->a_status, sizeof(int32_t));
   if (!ok) return fail(FM_ERR_ALLOC, "hipMalloc of the adjoint workspace failed");
-  if (hipMemset(p->a_part, 0, sizeof(double) * 2 * p->part_rows * kMaxK) != hipSuccess ||
-      hipMemset(p->aS, 0, sizeof(fm::State) * 2) != hipSuccess)
+  if (hipMemsetAsync(p->a_part, 0, sizeof(double) * 2 * p->part_rows * kMaxK, s) != hipSuccess ||
+      hipMemsetAsync(p->aS, 0, sizeof(fm::State) * 2, s) != hipSuccess)
     return fail(FM_ERR_HIP, "hipMemset of the adjoint state failed");
   if (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_BLOCKRB && !p->wf.ff) {
-    fm_status fs = alloc_faces(p);  // its CG is preconditioned in natural order
+    fm_status fs = alloc_faces(p, s);  // its CG is preconditioned in natural order
     if (fs) return fs;
   }
   if (!p->a_host && hipHostMalloc((void **)&p->a_host, sizeof(fm::State) * 2, hipHostMallocDefault) != hipSuccess)
@@ -1546,7 +1549,7 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
       p->wf_pack_grid = (int)std::min<int64_t>(8 * kMaxGrid, (units + wpb - 1) / wpb);
       p->wf_unpack_grid = (int)std::min<int64_t>(kMaxGrid, (int64_t)w.ntiles * ((prm->nz + fm::kUnpackZ - 1) / fm::kUnpackZ));
       if (prm->ordering == FM_ORDER_NATURAL) {
-        fm_status fs = alloc_faces(p);
+        fm_status fs = alloc_faces(p, nullptr);
         if (fs) return cleanup(fs);
       }
     }
@@ -1636,6 +1639,9 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
   }
   if (hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking) != hipSuccess)
     return cleanup(fail(FM_ERR_HIP, "hipStreamCreate failed"));
+  // the plan's arrays are cleared on the default stream, which other streams need not wait for
+  if (hipStreamSynchronize(nullptr) != hipSuccess)
+    return cleanup(fail(FM_ERR_HIP, "clearing the plan's arrays failed"));
   *out = p;
   return FM_OK;
 }
@@ -1924,7 +1930,7 @@ fm_status fm_adjoint(fm_plan *p, const double *dldf, const void *sens, void *dld
   if (maxit < 0 || !(rtol >= 0.0) || !std::isfinite(rtol)) return fail(FM_ERR_ARG, "maxit must be >= 0 and rtol finite, >= 0");
   if (!p->solved) return fail(FM_ERR_STATE, "fm_adjoint needs a converged map from fm_solve or fm_iterate");
   if (p->ict) return fail(FM_ERR_ARG, "fm_adjoint preconditions with IC(0), the diagonal or nothing, not IC_t");
-  fm_status st = adj_alloc(p);
+  fm_status st = adj_alloc(p, s);
   if (st) return st;
   FM_HIP(hipMemsetAsync(p->a_status, 0, sizeof(int32_t), s));
   fm::State out{};
