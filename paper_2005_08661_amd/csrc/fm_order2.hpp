@@ -384,7 +384,7 @@ __global__ __launch_bounds__(kNT) void k_diag2(IterArgs<T> a0, const T *__restri
   const double beta = a.beta;
   double acc[2] = {0.0, 0.0};
   int bad = 0;
-  for (; base < n; base += stride) {
+  for (; base < n && !st.cg_done; base += stride) {
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       const int j = base + v * kNT + (int)threadIdx.x;

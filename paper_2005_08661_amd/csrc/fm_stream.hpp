@@ -273,7 +273,7 @@ __global__ __launch_bounds__(kNT) void k_rb_black(IterArgs<T> a0, const T *__res
   const double beta = a.beta, b2 = a.beta * a.beta;
   double acc[2] = {0.0, 0.0};
   int bad = 0;
-  for (; base < n; base += stride) {
+  for (; base < n && !st.cg_done; base += stride) {
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       const int j = base + v * kNT + (int)threadIdx.x;
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(kNT) void k_rb_red(IterArgs<T> a0, const T *__restr
   const double beta = a.beta;
   double acc[2] = {0.0, 0.0};
   int bad = 0;
-  for (; base < n; base += stride) {
+  for (; base < n && !st.cg_done; base += stride) {
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       const int j = base + v * kNT + (int)threadIdx.x;
@@ -724,7 +724,7 @@ __global__ __launch_bounds__(kNT) void k_diag(IterArgs<T> a0, const T *__restric
   const double beta = a.beta;
   double acc[2] = {0.0, 0.0};
   int bad = 0;
-  for (; base < n; base += stride) {
+  for (; base < n && !st.cg_done; base += stride) {
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       const int j = base + v * kNT + (int)threadIdx.x;
