@@ -136,9 +136,15 @@ typedef struct fm_plan fm_plan;
 
 /* Validate the parameters and allocate the plan's device workspace on the
  * current device (about 70 B per voxel in MIX, 140 B in F64, some 20 B (MIX)
- * to 40 B (F64) more for IC(0) with second-order differences, some 25 B (MIX)
- * to 30 B (F64) more for IC(0) in natural or block red-black order, plus the
- * reduction buffers).  *plan is set to NULL on failure. */
+ * to 40 B (F64) more for IC(0) with second-order differences, plus the
+ * reduction buffers).  IC(0) in natural or block red-black order and IC_t of
+ * levels 0 and 1 sweep over rows that hold nz + 15 (IC_t: up to nz + 21) steps
+ * a column: for columns of 64 voxels some 25 to 35 B per voxel more, IC_t 170 B,
+ * and per voxel the more the shorter the columns.  Rows of more than 4 GiB and
+ * 64 B per voxel (IC_t 256 B), or for which the device has no memory, are not
+ * taken: the plan then runs a launch per level of the elimination, with the
+ * same results (IC_t: 48 B per voxel at level 0, 72 at level 1, 112 at level
+ * 2, which always does).  *plan is set to NULL on failure. */
 fm_status fm_plan_create(const fm_params *prm, fm_plan **plan);
 
 /* Free the plan and its workspace.  NULL is accepted. */

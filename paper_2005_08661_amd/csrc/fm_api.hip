@@ -24,6 +24,7 @@
 #include "fm_order2.hpp"
 #include "fm_ict.hpp"
 #include "fm_ict_tile.hpp"
+#include "fm_level.hpp"
 #include "fm_tile.hpp"
 
 using fm::kBlock;
@@ -88,6 +89,8 @@ struct fm_plan {
   size_t part_rows = kMaxGrid;
   fm::Wavefront wf{};          // natural-order sweep: tiles, tickets, packed arrays, face buffers
   int wf_pack_grid = 1, wf_unpack_grid = 1;
+  void *wf_bases[4] = {};      // allocations of the packed rows and face buffers
+  bool by_levels = false;      // no packed rows: natural and block red-black IC(0) run a launch per level
   double *setup_part = nullptr;
   double *nmask = nullptr;
   int32_t *status = nullptr;
@@ -118,6 +121,7 @@ struct fm_plan {
   std::map<std::vector<int64_t>, std::pair<hipGraph_t, hipGraphExec_t>> graphs;
   // implicit adjoint workspace (allocated by the first fm_adjoint call)
   bool adj_ready = false;
+  bool adj_levels = false;  // block red-black plan without face buffers: its CG runs a launch per level
   void *aR = nullptr, *aZ = nullptr, *aX = nullptr, *aDc = nullptr, *aH = nullptr, *aV = nullptr;
   void *aDd[2] = {nullptr, nullptr};
   double *a_hinv = nullptr, *a_ipiv = nullptr, *a_part = nullptr;
@@ -139,7 +143,7 @@ struct fm_plan {
   int ict_noff = 0, ict_nlev = 0, ict_kcol = 0, ict_blocks = 0;
   double *ict_lo = nullptr, *ict_ld = nullptr, *ict_y = nullptr, *ict_pd = nullptr;
   double *ict_hmax = nullptr, *ict_hpart = nullptr;
-  bool ict_tiled = false;      // fill levels 0 and 1: one launch per sweep
+  bool ict_tiled = false;      // fill levels 0 and 1, where the packed rows fit: one launch per sweep
   fm::IctSweep ict_sweep{};
   int ict_pack_grid = 1, ict_unpack_grid = 1;
 };
@@ -375,10 +379,9 @@ fm_status enqueue_ict_tiled(fm_plan *p, const T *g, const fm::IterArgs<T> &a, co
   return FM_OK;
 }
 
-// Fill level 2: a launch per level of the schedule.
-template <typename T>
+// Fill level 2, and volumes whose packed rows do not fit: a launch per level of the schedule.
+template <typename T, int LEVEL>
 fm_status enqueue_ict_levels(fm_plan *p, const T *g, hipStream_t s, Recorder *rec) {
-  constexpr int LEVEL = 2;
   fm::IctArgs<T> a{};
   a.geo = p->geo;
   a.beta = p->prm.beta;
@@ -444,6 +447,28 @@ fm_status enqueue_block(fm_plan *p, const fm::IterArgs<T> &ain, const fm::IterAr
   return FM_OK;
 }
 
+// Either order without packed rows: the levels of both sweeps (outside the state
+// chain), then the dot products.
+template <typename T, bool BLOCK>
+fm_status enqueue_ic_levels(fm_plan *p, const fm::IterArgs<T> &ia, const T *gsrc, hipStream_t s, Recorder *rec) {
+  const fm::Geo &g = p->geo;
+  const int per_x = BLOCK ? g.ny : std::min(g.ny, g.nz), nlev = BLOCK ? g.nz + 2 * (fm::kTile - 1) : g.nx + g.ny + g.nz - 2;
+  fm::LevelArgs<T> a{g,     ia.beta, ia.code, ia.D, gsrc ? gsrc : ((ia.par & 1) ? ia.G[1] : ia.G[0]),
+                     ia.X,  ia.P,    ia.ipiv, ia.status, per_x};
+  const dim3 grid((unsigned)(((int64_t)g.nx * per_x + fm::kLevelNT - 1) / fm::kLevelNT));
+  for (int c = 0; c < (BLOCK ? 2 : 1); ++c)
+    for (int lv = 0; lv < nlev; ++lv)
+      FM_LAUNCH(FM_K_PRECOND_A, (fm::k_ic_level_fwd<T, BLOCK>), grid, dim3(fm::kLevelNT), s, a, lv, c);
+  FM_LAUNCH_CHECK();
+  for (int c = BLOCK ? 1 : 0; c >= 0; --c)
+    for (int lv = nlev - 1; lv >= 0; --lv)
+      FM_LAUNCH(FM_K_PRECOND_B, (fm::k_ic_level_bwd<T, BLOCK>), grid, dim3(fm::kLevelNT), s, a, lv, c);
+  FM_LAUNCH_CHECK();
+  FM_LAUNCH(FM_K_DOTS, (fm::k_ict_dots<T, T>), dim3(p->sgrid), dim3(fm::kNT), s, ia, (const T *)ia.P, gsrc);
+  FM_LAUNCH_CHECK();
+  return FM_OK;
+}
+
 template <typename T>
 fm_status enqueue_precond(fm_plan *p, const T *gsrc, hipStream_t s, Recorder *rec = nullptr) {
   auto pargs = [&](fm_plan *pp, uint64_t q) {
@@ -463,9 +488,11 @@ fm_status enqueue_precond(fm_plan *p, const T *gsrc, hipStream_t s, Recorder *re
       set_parts(p, p->ict_unpack_grid, 2);
       return FM_OK;
     }
-    st = enqueue_ict_levels<T>(p, g, s, rec);
+    st = p->prm.ict_level == 0   ? enqueue_ict_levels<T, 0>(p, g, s, rec)
+         : p->prm.ict_level == 1 ? enqueue_ict_levels<T, 1>(p, g, s, rec)
+                                 : enqueue_ict_levels<T, 2>(p, g, s, rec);
     if (st) return st;
-    FM_LAUNCH(FM_K_DOTS, fm::k_ict_dots<T>, dim3(p->sgrid), dim3(fm::kNT), s, pargs(p, p->q++),
+    FM_LAUNCH(FM_K_DOTS, (fm::k_ict_dots<T, double>), dim3(p->sgrid), dim3(fm::kNT), s, pargs(p, p->q++),
               (const double *)p->ict_pd, gsrc);
     FM_LAUNCH_CHECK();
     set_parts(p, p->sgrid, 2);
@@ -483,6 +510,12 @@ fm_status enqueue_precond(fm_plan *p, const T *gsrc, hipStream_t s, Recorder *re
     FM_LAUNCH(FM_K_PRECOND_B, (fm::k_ic3_bwd0<T>), dim3(p->sgrid), dim3(fm::kNT), s, pargs(p, p->q++), gsrc);
     FM_LAUNCH_CHECK();
     set_parts(p, 0, 0);
+  } else if (p->by_levels) {
+    const fm::IterArgs<T> a = pargs(p, p->q++);
+    fm_status st = p->prm.ordering == FM_ORDER_BLOCKRB ? enqueue_ic_levels<T, true>(p, a, gsrc, s, rec)
+                                                       : enqueue_ic_levels<T, false>(p, a, gsrc, s, rec);
+    if (st) return st;
+    set_parts(p, p->sgrid, 2);
   } else if (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_BLOCKRB) {
     const fm::IterArgs<T> ain = pargs(p, p->q++);
     set_parts(p, 0, 0);
@@ -525,6 +558,7 @@ uint64_t launches_per_iteration(const fm_plan *p) {
   if (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_NATURAL) precond_dir = 3;
   if (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_COLOR3) precond_dir = 5;
   if (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_BLOCKRB) precond_dir = 3;
+  if (p->by_levels) precond_dir = 2;
   return 1 + precond_dir + (uint64_t)(p->prm.nmls - 1);
 }
 
@@ -807,7 +841,10 @@ fm_status validate(const fm_params *p) {
 
 bool plan_alloc(fm_plan *p, void **ptr, size_t bytes) {
   void *b = nullptr;
-  if (hipMalloc(&b, bytes ? bytes : 1) != hipSuccess) return false;
+  if (hipMalloc(&b, bytes ? bytes : 1) != hipSuccess) {
+    (void)hipGetLastError();  // (the caller may have another way; a later launch must not see the error)
+    return false;
+  }
   p->bases.push_back(b);
   *ptr = b;
   return true;
@@ -836,16 +873,35 @@ bool sweeps_in_tiles(const fm_plan *p) {
   return p->prm.precond == FM_PRECOND_IC0 && (p->prm.ordering == FM_ORDER_NATURAL || p->prm.ordering == FM_ORDER_BLOCKRB);
 }
 
+// Free what the plan has allocated since it had `mark` allocations.
+void plan_free_from(fm_plan *p, size_t mark) {
+  while (p->bases.size() > mark) {
+    (void)hipFree(p->bases.back());
+    p->bases.pop_back();
+  }
+}
+
+// Packed rows hold the steps of a tile's skew too, so short columns make them many times
+// the volume.  They are taken up to 4 GiB, beyond that up to `per_voxel` bytes a voxel: a
+// plan's memory stays within that of the forms that need none.  (The 4 GiB are reached by
+// a single slice of 2400x2400 in F64, or by 30 million voxels in columns of 10.)
+bool packed_rows_fit(size_t bytes, size_t n, size_t per_voxel) {
+  return bytes <= std::max((size_t)4 << 30, per_voxel * n);
+}
+
+size_t face_values(const fm::Wavefront &w) { return ((size_t)w.ntiles + 1) * w.frow * fm::kFaceSlots; }
+
 // Face buffers and tickets of the natural-order sweeps: rows past a sweep and
 // the last tile (no neighbour) stay 0.  Cleared on the stream whose sweeps come first.
 fm_status alloc_faces(fm_plan *p, hipStream_t s) {
   fm::Wavefront &w = p->wf;
-  w.frow = w.nrow + fm::kNatU + fm::kTile - 1;
-  const size_t faces = ((size_t)w.ntiles + 1) * w.frow * fm::kFaceSlots;
+  const size_t faces = face_values(w);
   void *ff = nullptr, *fp = nullptr, *tk = nullptr;
   if (!plan_alloc(p, &ff, sizeof(fm::Rec) * faces) || !plan_alloc(p, &fp, p->tsize * faces) ||
       !plan_alloc(p, &tk, sizeof(uint32_t) * 2))
     return fail(FM_ERR_ALLOC, "hipMalloc of the face buffers failed");
+  p->wf_bases[2] = ff;
+  p->wf_bases[3] = fp;
   if (hipMemsetAsync(ff, 0, sizeof(fm::Rec) * faces, s) != hipSuccess ||
       hipMemsetAsync(fp, 0, p->tsize * faces, s) != hipSuccess)
     return fail(FM_ERR_HIP, "hipMemset of the face buffers failed");
@@ -855,7 +911,49 @@ fm_status alloc_faces(fm_plan *p, hipStream_t s) {
   return FM_OK;
 }
 
-// Tables and arrays of the tiled IC_t sweeps (fm_ict_tile.hpp).
+// The face buffers have been freed.
+void drop_faces(fm_plan *p) {
+  p->wf.ff = nullptr;
+  p->wf_bases[2] = p->wf_bases[3] = nullptr;
+}
+
+// Packed rows of the natural and block red-black sweeps, or what a launch per level takes
+// in their place (the face buffers are the natural order's; a block red-black plan gets
+// them with the adjoint's workspace).
+fm_status alloc_sweep_rows(fm_plan *p) {
+  fm::Wavefront &w = p->wf;
+  const int U = fm::kNatU, nz = p->geo.nz;
+  w.nrow = (nz + 2 * (fm::kTile - 1) + 1 + 2 * U - 1) / (2 * U) * (2 * U);
+  w.trow = w.nrow + fm::kTile;
+  w.frow = w.nrow + U + fm::kTile - 1;
+  const size_t guard = (size_t)(U + fm::kTile) * 64;  // rows read past either end
+  const size_t packed = ((size_t)w.ntiles + 1) * w.trow * 64 + 2 * guard, value = sizeof(fm::Rec) + p->tsize;
+  const bool natural = p->prm.ordering == FM_ORDER_NATURAL;
+  const size_t mark = p->bases.size();
+  void *rec = nullptr, *pv = nullptr;
+  if (!packed_rows_fit(value * (packed + (natural ? face_values(w) : 0)), (size_t)p->n, 64) ||
+      !plan_alloc(p, &rec, sizeof(fm::Rec) * packed) || !plan_alloc(p, &pv, p->tsize * packed) ||
+      (natural && alloc_faces(p, nullptr) != FM_OK)) {
+    plan_free_from(p, mark);
+    drop_faces(p);
+    p->by_levels = true;
+    if (!plan_alloc_padded(p, &p->X, (size_t)p->n, p->tsize)) return fail(FM_ERR_ALLOC, "hipMalloc of p->X failed");
+    return FM_OK;
+  }
+  p->wf_bases[0] = rec;
+  p->wf_bases[1] = pv;
+  if (hipMemset(rec, 0, sizeof(fm::Rec) * packed) != hipSuccess || hipMemset(pv, 0, p->tsize * packed) != hipSuccess)
+    return fail(FM_ERR_HIP, "hipMemset of the sweep arrays failed");
+  w.rec = (fm::Rec *)rec + guard;
+  w.p = (char *)pv + p->tsize * guard;
+  const int64_t units = (int64_t)w.ntiles * w.nrow, wpb = fm::kNT / fm::kWave;
+  p->wf_pack_grid = (int)std::min<int64_t>(8 * kMaxGrid, (units + wpb - 1) / wpb);
+  p->wf_unpack_grid = (int)std::min<int64_t>(kMaxGrid, (int64_t)w.ntiles * ((nz + fm::kUnpackZ - 1) / fm::kUnpackZ));
+  return FM_OK;
+}
+
+// Tables and arrays of the tiled IC_t sweeps (fm_ict_tile.hpp); leaves ict_tiled unset
+// where their packed rows do not fit.
 template <int LEVEL>
 fm_status alloc_ict_sweep(fm_plan *p) {
   using C = fm::IctTile<LEVEL>;
@@ -875,10 +973,14 @@ fm_status alloc_ict_sweep(fm_plan *p) {
   const size_t row = (size_t)C::planes * 64, packed = ((size_t)w.ntiles * w.nrow + 2 * U) * row;
   const size_t faces = ((size_t)w.ntiles + 1) * w.frow * fm::kFaceSlots;
   void *ord = nullptr, *tk = nullptr, *rec = nullptr, *ff = nullptr, *fb = nullptr;
-  if (!plan_alloc(p, &ord, sizeof(int2) * order.size()) || !plan_alloc(p, &tk, sizeof(uint32_t) * 2) ||
+  const size_t mark = p->bases.size();
+  if (!packed_rows_fit(sizeof(fm::Rec) * (packed + faces * (C::fr + C::br)), (size_t)p->n, 256) ||
+      !plan_alloc(p, &ord, sizeof(int2) * order.size()) || !plan_alloc(p, &tk, sizeof(uint32_t) * 2) ||
       !plan_alloc(p, &rec, sizeof(fm::Rec) * packed) || !plan_alloc(p, &ff, sizeof(fm::Rec) * faces * C::fr) ||
-      !plan_alloc(p, &fb, sizeof(fm::Rec) * faces * C::br))
-    return fail(FM_ERR_ALLOC, "hipMalloc of the IC_t sweep arrays failed");
+      !plan_alloc(p, &fb, sizeof(fm::Rec) * faces * C::br)) {
+    plan_free_from(p, mark);
+    return FM_OK;
+  }
   if (hipMemcpy(ord, order.data(), sizeof(int2) * order.size(), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemset(rec, 0, sizeof(fm::Rec) * packed) != hipSuccess)
     return fail(FM_ERR_HIP, "set-up of the IC_t sweep arrays failed");
@@ -899,12 +1001,35 @@ fm_status alloc_ict_sweep(fm_plan *p) {
 
 fm_status wf_init(fm_plan *p, double *f0, hipStream_t s);  // fm_waterfat.inc
 
-void free_plan(fm_plan *p) {
-  if (!p) return;
+void drop_graphs(fm_plan *p) {
   for (auto &kv : p->graphs) {
     if (kv.second.second) (void)hipGraphExecDestroy(kv.second.second);
     if (kv.second.first) (void)hipGraphDestroy(kv.second.first);
   }
+  p->graphs.clear();
+}
+
+// Give the packed rows back for memory that is needed otherwise; later calls run a
+// launch per level.  False where there are none.
+bool give_back_rows(fm_plan *p) {
+  if (!sweeps_in_tiles(p) || p->by_levels || hipDeviceSynchronize() != hipSuccess) return false;
+  drop_graphs(p);  // they hold launches on the packed rows
+  for (void *&b : p->wf_bases) {
+    const auto it = std::find(p->bases.begin(), p->bases.end(), b);
+    if (b && it != p->bases.end()) {
+      (void)hipFree(b);
+      p->bases.erase(it);
+    }
+    b = nullptr;
+  }
+  drop_faces(p);
+  p->by_levels = true;
+  return plan_alloc_padded(p, &p->X, (size_t)p->n, p->tsize);
+}
+
+void free_plan(fm_plan *p) {
+  if (!p) return;
+  drop_graphs(p);
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
   for (hipEvent_t e : p->a_copied)
     if (e) (void)hipEventDestroy(e);
@@ -1091,9 +1216,8 @@ fm_status run_graph(fm_plan *p, int niter, hipStream_t s);
 fm_status run_iterations(fm_plan *p, int niter, hipStream_t s) {
   if (niter <= 0) return FM_OK;
   if (use_resident(p)) return run_resident(p, niter, s);
-  if (!p->ict || p->ict_tiled) return run_graph(p, niter, s);
-  // IC_t of fill level 2 launches a kernel per wavefront level (thousands per iteration): one
-  // graph of one iteration, replayed niter times
+  if (!p->by_levels && (!p->ict || p->ict_tiled)) return run_graph(p, niter, s);
+  // a launch per level (thousands per iteration): one graph of one iteration, replayed niter times
   for (int i = 0; i < niter; ++i) {
     fm_status st = run_graph(p, 1, s);
     if (st) return st;
@@ -1171,21 +1295,32 @@ fm_status read_status(fm_plan *p, hipStream_t s, int32_t *status) {
 fm_status adj_alloc(fm_plan *p, hipStream_t s) {
   if (p->adj_ready) return FM_OK;
   const size_t n = (size_t)p->n, ts = p->tsize;
-  bool ok = plan_alloc_padded(p, &p->aR, n, ts) && plan_alloc_padded(p, &p->aZ, n, ts) &&
-            plan_alloc_padded(p, &p->aX, n, ts) && plan_alloc_padded(p, &p->aDc, n, ts) &&
-            plan_alloc_padded(p, &p->aH, n, ts) && plan_alloc_padded(p, &p->aV, n, ts) &&
-            plan_alloc_padded(p, &p->aDd[0], n, ts) && plan_alloc_padded(p, &p->aDd[1], n, ts) &&
-            plan_alloc_padded(p, (void **)&p->a_hinv, n, sizeof(double)) &&
-            plan_alloc_padded(p, (void **)&p->a_ipiv, n, sizeof(double)) &&
-            plan_alloc(p, (void **)&p->a_part, sizeof(double) * 2 * p->part_rows * kMaxK) &&
-            plan_alloc(p, (void **)&p->aS, sizeof(fm::State) * 2) && plan_alloc(p, (void **)&p->a_status, sizeof(int32_t));
-  if (!ok) return fail(FM_ERR_ALLOC, "hipMalloc of the adjoint workspace failed");
+  auto take = [&]() {
+    const size_t mark = p->bases.size();
+    const bool ok = plan_alloc_padded(p, &p->aR, n, ts) && plan_alloc_padded(p, &p->aZ, n, ts) &&
+                    plan_alloc_padded(p, &p->aX, n, ts) && plan_alloc_padded(p, &p->aDc, n, ts) &&
+                    plan_alloc_padded(p, &p->aH, n, ts) && plan_alloc_padded(p, &p->aV, n, ts) &&
+                    plan_alloc_padded(p, &p->aDd[0], n, ts) && plan_alloc_padded(p, &p->aDd[1], n, ts) &&
+                    plan_alloc_padded(p, (void **)&p->a_hinv, n, sizeof(double)) &&
+                    plan_alloc_padded(p, (void **)&p->a_ipiv, n, sizeof(double)) &&
+                    plan_alloc(p, (void **)&p->a_part, sizeof(double) * 2 * p->part_rows * kMaxK) &&
+                    plan_alloc(p, (void **)&p->aS, sizeof(fm::State) * 2) &&
+                    plan_alloc(p, (void **)&p->a_status, sizeof(int32_t));
+    if (!ok) plan_free_from(p, mark);
+    return ok;
+  };
+  if (!take() && !(give_back_rows(p) && take())) return fail(FM_ERR_ALLOC, "hipMalloc of the adjoint workspace failed");
   if (hipMemsetAsync(p->a_part, 0, sizeof(double) * 2 * p->part_rows * kMaxK, s) != hipSuccess ||
       hipMemsetAsync(p->aS, 0, sizeof(fm::State) * 2, s) != hipSuccess)
     return fail(FM_ERR_HIP, "hipMemset of the adjoint state failed");
-  if (p->prm.precond == FM_PRECOND_IC0 && p->prm.ordering == FM_ORDER_BLOCKRB && !p->wf.ff) {
-    fm_status fs = alloc_faces(p, s);  // its CG is preconditioned in natural order
-    if (fs) return fs;
+  if (sweeps_in_tiles(p) && !p->by_levels && !p->wf.ff) {
+    // a block red-black plan's CG is preconditioned in natural order, where the face buffers fit
+    const size_t mark = p->bases.size();
+    p->adj_levels = !packed_rows_fit((sizeof(fm::Rec) + ts) * face_values(p->wf), n, 64) || alloc_faces(p, s) != FM_OK;
+    if (p->adj_levels) {
+      plan_free_from(p, mark);
+      drop_faces(p);
+    }
   }
   if (!p->a_host && hipHostMalloc((void **)&p->a_host, sizeof(fm::State) * 2, hipHostMallocDefault) != hipSuccess)
     return fail(FM_ERR_ALLOC, "pinned memory for the adjoint state failed");
@@ -1294,7 +1429,12 @@ fm_status adj_enqueue_iteration(fm_plan *p, uint64_t &q, int &np, int &nv, int k
     nv = 2;
   } else if (p->prm.precond == FM_PRECOND_IC0) {
     // natural-order IC(0) also for block red-black plans (v does not depend on the preconditioner)
-    if (p->prm.ordering == FM_ORDER_NATURAL || p->prm.ordering == FM_ORDER_BLOCKRB) {
+    if (p->by_levels || p->adj_levels) {
+      fm_status e = enqueue_ic_levels<T, false>(p, adj_precond_args<T>(p, q++, np, nv), r, s, rec);
+      if (e) return e;
+      np = p->sgrid;
+      nv = 2;
+    } else if (p->prm.ordering == FM_ORDER_NATURAL || p->prm.ordering == FM_ORDER_BLOCKRB) {
       const fm::IterArgs<T> ain = adj_precond_args<T>(p, q++, np, nv);
       fm_status e = enqueue_natural<T>(p, ain, adj_precond_args<T>(p, q++, 0, 0), r, p->a_status, s, rec);
       if (e) return e;
@@ -1497,9 +1637,9 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
   } else {
     for (int i = 0; i < 2; ++i) FM_ALLOC_PAD(p->G[i], ts);
     FM_ALLOC_PAD(p->D, ts);
-    if (!sweeps_in_tiles(p)) FM_ALLOC_PAD(p->X, ts);
+    if (!sweeps_in_tiles(p) && prm->precond != FM_PRECOND_ICT) FM_ALLOC_PAD(p->X, ts);
     FM_ALLOC_PAD(p->P, ts);
-    FM_ALLOC_PAD(p->ipiv, sizeof(double));
+    if (prm->precond != FM_PRECOND_ICT) FM_ALLOC_PAD(p->ipiv, sizeof(double));  // (IC_t's pivots are L_jj^2)
   }
   FM_ALLOC_PAD(p->hinv, sizeof(double));
   FM_ALLOC(p->S, sizeof(fm::State) * 2);
@@ -1535,28 +1675,6 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
         return cleanup(fail(FM_ERR_HIP, "block tables upload failed"));
       w.blk[c] = (const int2 *)bp;
     }
-    if (sweeps_in_tiles(p)) {
-      // packed arrays of the natural and block red-black sweeps; the face buffers are the natural
-      // order's (a block red-black plan gets them with the adjoint's workspace)
-      const int U = fm::kNatU;
-      w.nrow = (prm->nz + 2 * (fm::kTile - 1) + 1 + 2 * U - 1) / (2 * U) * (2 * U);
-      w.trow = w.nrow + fm::kTile;
-      const size_t guard = (size_t)(U + fm::kTile) * 64;  // rows read past either end
-      const size_t packed = ((size_t)w.ntiles + 1) * w.trow * 64 + 2 * guard;
-      FM_ALLOC(w.rec, sizeof(fm::Rec) * packed);
-      FM_ALLOC(w.p, ts * packed);
-      if (hipMemset(w.rec, 0, sizeof(fm::Rec) * packed) != hipSuccess || hipMemset(w.p, 0, ts * packed) != hipSuccess)
-        return cleanup(fail(FM_ERR_HIP, "hipMemset of the sweep arrays failed"));
-      w.rec += guard;
-      w.p = (char *)w.p + ts * guard;
-      const int64_t units = (int64_t)w.ntiles * w.nrow, wpb = fm::kNT / fm::kWave;
-      p->wf_pack_grid = (int)std::min<int64_t>(8 * kMaxGrid, (units + wpb - 1) / wpb);
-      p->wf_unpack_grid = (int)std::min<int64_t>(kMaxGrid, (int64_t)w.ntiles * ((prm->nz + fm::kUnpackZ - 1) / fm::kUnpackZ));
-      if (prm->ordering == FM_ORDER_NATURAL) {
-        fm_status fs = alloc_faces(p, nullptr);
-        if (fs) return cleanup(fs);
-      }
-    }
     p->part_rows = (size_t)(w.ntiles > kMaxGrid ? w.ntiles : kMaxGrid);
   }
   FM_ALLOC(p->part, sizeof(double) * 2 * p->part_rows * kMaxK);
@@ -1568,6 +1686,17 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
   if (p->res_ok) {
     FM_ALLOC(p->res_part, sizeof(double) * fm::kResSlots * kMaxK * (size_t)p->res_grid);
     FM_ALLOC(p->res_bar, res_bar_bytes(p));
+  }
+  if (prm->model == FM_WATERFAT) {
+    FM_ALLOC(p->rho, sizeof(double) * n);
+    FM_ALLOC(p->gabs, sizeof(double) * L * L);
+    FM_ALLOC(p->wf_tmp, sizeof(double) * n * 4);
+    FM_ALLOC(p->sweep_rot, sizeof(double2) * L * L);
+  }
+  // the packed rows last, so that they take no memory that something else needs
+  if (sweeps_in_tiles(p)) {
+    fm_status rs = alloc_sweep_rows(p);
+    if (rs) return cleanup(rs);
   }
   if (prm->precond == FM_PRECOND_ICT) {
     int noff = 0, wa = 1, wb = 1;
@@ -1585,7 +1714,8 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
     if (prm->ict_level < 2) {
       fm_status is = prm->ict_level == 0 ? alloc_ict_sweep<0>(p) : alloc_ict_sweep<1>(p);
       if (is) return cleanup(is);
-    } else {
+    }
+    if (!p->ict_tiled) {
       p->ict_nlev = wa * (prm->nx - 1) + wb * (prm->ny - 1) + (prm->nz - 1) + 1;
       p->ict_kcol = (prm->nz - 1) / wb + 1;
       p->ict_blocks = (int)(((int64_t)prm->nx * p->ict_kcol + fm::kIctNT - 1) / fm::kIctNT);
@@ -1597,12 +1727,6 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
           hipMemset(p->ict_ld, 0, sizeof(double) * n) != hipSuccess)
         return cleanup(fail(FM_ERR_HIP, "hipMemset of the IC_t factor failed"));
     }
-  }
-  if (prm->model == FM_WATERFAT) {
-    FM_ALLOC(p->rho, sizeof(double) * n);
-    FM_ALLOC(p->gabs, sizeof(double) * L * L);
-    FM_ALLOC(p->wf_tmp, sizeof(double) * n * 4);
-    FM_ALLOC(p->sweep_rot, sizeof(double2) * L * L);
   }
 #undef FM_ALLOC
 #undef FM_ALLOC_PAD
@@ -1954,11 +2078,7 @@ fm_status fm_set_beta(fm_plan *p, double beta) {
   fm_status cs = check_plan(p);
   if (cs) return cs;
   if (!(beta >= 0.0) || !std::isfinite(beta)) return fail(FM_ERR_ARG, "beta must be finite and >= 0");
-  for (auto &kv : p->graphs) {
-    if (kv.second.second) (void)hipGraphExecDestroy(kv.second.second);
-    if (kv.second.first) (void)hipGraphDestroy(kv.second.first);
-  }
-  p->graphs.clear();
+  drop_graphs(p);
   p->prm.beta = beta;
   p->solved = false;
   return FM_OK;

@@ -9,8 +9,8 @@
 // largest magnitude in H), and L_jj = sqrt(H_jj - sum_k L_jk^2).  The solves
 // are L y = g in natural order and L^T p = y in reverse.
 //
-// Schedule (fill level 2; levels 0 and 1 run one launch per sweep,
-// fm_ict_tile.hpp): every offset o = (dx, dy, dz) of the pattern satisfies
+// Schedule (fill level 2; levels 0 and 1 run one launch per sweep, fm_ict_tile.hpp,
+// unless its packed rows would take too much memory): every offset o = (dx, dy, dz) of the pattern satisfies
 // a dx + b dy + dz >= 1 for the level's weights (a, b) (level 0: 1, 1;
 // level 1: 3, 2; level 2: 7, 3), so the voxels with a x + b y + z = s depend
 // only on voxels of smaller s.  One launch handles one such level s (the
@@ -267,10 +267,10 @@ __global__ __launch_bounds__(kIctNT) void k_ict_bwd(IctArgs<T> a, int s) {
   a.P[j] = (T)p;
 }
 
-// Conjugacy dot products g^T p and g_prev^T p (p from the IC_t solves, FP64),
-// in the chain of scalar state like the other preconditioner passes.
-template <typename T>
-__global__ __launch_bounds__(kNT) void k_ict_dots(IterArgs<T> a0, const double *__restrict__ pd,
+// Conjugacy dot products g^T p and g_prev^T p (p from the IC_t solves in FP64, or from
+// the IC(0) levels), in the chain of scalar state like the other preconditioner passes.
+template <typename T, typename TP>
+__global__ __launch_bounds__(kNT) void k_ict_dots(IterArgs<T> a0, const TP *__restrict__ pd,
                                                   const T *__restrict__ gsrc) {
   const VolView vw = vol_view<false>(a0);
   const VArgs<T> a = at_volume<false>(a0, vw);
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(kNT) void k_ict_dots(IterArgs<T> a0, const double *
   double acc[2] = {0.0, 0.0};
   for (int j = (int)(blockIdx.x * kNT + threadIdx.x); j < n; j += (int)(gridDim.x * kNT)) {
     if (!(a.code[j] & NB_SELF)) continue;
-    const double p = pd[j];
+    const double p = (double)pd[j];
     acc[0] += (double)gg[j] * p;
     acc[1] += (double)a.Gp[j] * p;
   }
