@@ -1174,16 +1174,26 @@ void plan_geometry(fm_plan *p, int32_t nz) {
   p->pad = (((p->reg2 ? 2 : 1) * p->geo.sx + 63) / 64) * 64;
 }
 
-// Volumes with no more voxels than threads in the largest grid (FP32, where four voxels a thread
-// pay from less on: half as many) give each voxel a thread of its own: a pass of such a volume lasts as long as one thread's chain, and two or four
-// voxels in it lengthen the chain while most of the chip idles (74x74x10 MIX 1.73 -> 1.36 ms
-// together with the tile passes' shorter runs, 51x66x15 1.35 -> 1.23, 32x32x16 F64 natural
-// 3.87 -> 3.70; 149x148x11 MIX, beyond the line: 1.89 ms, 1.80 in fours).  Second-order volumes that take the four-voxel passes stay with them and
-// their grid (49x52x52: 2.18 ms, 2.28 with a thread per voxel).
+// Small volumes give each voxel a thread of its own: a pass of such a volume lasts as long as
+// one thread's chain, and two or four voxels in it lengthen the chain while most of the chip
+// idles.  The lines, each with both sides' times (voxels in fours or twos -> a thread each):
+// - FP32: half the threads of the largest grid.  115 200 voxels, second order 973 -> 894 us, red-
+//   black 639 -> 577; 163 840 voxels, red-black 582 and 583 (149x148x11: 1.80 -> 1.89 ms).
+//   Second-order volumes that take the four-voxel passes stay with them (49x52x52: 2.18, 2.28 ms).
+// - FP64, IC(0) or more than 4 echoes: three quarters of them.  192 512 voxels, red-black 804 ->
+//   793 us, six echoes 1197 -> 1153; 221 184 voxels, 787 -> 851 and 1220 -> 1280.
+// - FP64 otherwise (the passes of the diagonal with few echoes are short, those of second order
+//   keep their own voxels per thread): a workgroup per compute unit.  62 208 voxels, diagonal 575 ->
+//   525 us, second order 648 -> 612; 92 400 voxels, 603 -> 621 and 682 -> 727.
 bool few_voxels(const fm_params &q) {
-  const int64_t most = (int64_t)kMaxGrid * fm::kNT / (q.precision == FM_PREC_MIX ? 2 : 1);
+  const bool order2 = q.reg_order == 2;
+  int64_t most = 65536;
+  if (q.precision == FM_PREC_MIX)
+    most = 131072;
+  else if (!order2 && (q.precond == FM_PRECOND_IC0 || q.precond == FM_PRECOND_ICT || q.necho > 4))
+    most = 196608;
   return (int64_t)q.nx * q.ny * q.nz <= most &&
-         !(q.reg_order == 2 && q.precision == FM_PREC_MIX && q.necho <= 6 && q.nz % 4 == 0);
+         !(order2 && q.precision == FM_PREC_MIX && q.necho <= 6 && q.nz % 4 == 0);
 }
 
 // Workgroups of the streaming iteration passes.
