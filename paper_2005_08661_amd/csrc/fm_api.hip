@@ -1513,13 +1513,15 @@ struct OpAdjoint {
     np = p->sgrid;
     nv = 1;
     // The state after a chunk is looked at once the next chunk is in the stream, so the GPU
-    // does not wait for the host: the passes find the state converged and do nothing.  The
-    // natural-order sweeps do not look at it (128x128x64 MIX: 0.2 ms an iteration, 7 us a
-    // wait), so there each chunk is waited for: 39.4 -> 38.5 ms for 158 iterations.
+    // does not wait for the host: the passes find the state converged and do nothing.  Not so
+    // after the first chunk, after which many small volumes have converged (3x3x3: 233 us, 326
+    // with a second chunk that does nothing), nor for the natural-order sweeps, which do not look
+    // at the state (128x128x64 MIX: 0.2 ms an iteration, 7 us a wait; 158 iterations 39.4 -> 38.5 ms).
     const bool ahead = !sweeps_in_tiles(p);
     int k = 0, slot = 0;
-    bool pending = false;
+    bool seen = true;  // the state after the chunk before
     while (k < maxit) {
+      const bool wait = !ahead || k == 0;
       const int chunk = (maxit - k) < kAdjCheck ? (maxit - k) : kAdjCheck;
       for (int i = 0; i < chunk; ++i, ++k) {
         fm_status e = adj_enqueue_iteration<T>(p, q, np, nv, k, s);
@@ -1527,12 +1529,12 @@ struct OpAdjoint {
       }
       fm_status e = adj_finish(p, q, np, nv, slot, s);
       if (e) return e;
-      const int seen = ahead ? slot ^ 1 : slot;
-      if (pending || !ahead) {
-        FM_HIP(hipEventSynchronize(p->a_copied[seen]));
-        if (p->a_host[seen].cg_done) break;
+      if (wait || !seen) {
+        const int look = wait ? slot : slot ^ 1;
+        FM_HIP(hipEventSynchronize(p->a_copied[look]));
+        if (p->a_host[look].cg_done) break;
       }
-      pending = true;
+      seen = wait;
       slot ^= 1;
     }
     if (maxit == 0) {
