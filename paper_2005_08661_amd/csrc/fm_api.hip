@@ -598,54 +598,49 @@ int tail_nparts(const fm_plan *p) {
   return ts.grid > 0 ? ts.grid : p->sgrid;
 }
 
+// The four-voxel passes of a plan (2-6 echoes).  With 2-4 echoes they load early where a thread has
+// two fours or more (at five and six the registers are too many; the second-order gradient has no such form).
+using QuadKernel = void (*)(fm::IterArgs<float>);
+struct QuadKernels {
+  QuadKernel grad, mls;
+};
+template <int NE>
+QuadKernels quad_kernels_of(bool order2, bool early) {
+  if constexpr (NE <= 4)
+    if (early) return {order2 ? fm::k_grad2_q<NE> : fm::k_grad_q<NE, false, true>, fm::k_mls_q<NE, false, true>};
+  return {order2 ? fm::k_grad2_q<NE> : fm::k_grad_q<NE, false>, fm::k_mls_q<NE, false>};
+}
+QuadKernels quad_kernels(const fm_plan *p) {
+  const bool early = p->n >= (int64_t)8 * kMaxGrid * fm::kNT;
+  switch (p->prm.necho) {
+    case 2: return quad_kernels_of<2>(p->reg2, early);
+    case 3: return quad_kernels_of<3>(p->reg2, early);
+    case 4: return quad_kernels_of<4>(p->reg2, early);
+    case 5: return quad_kernels_of<5>(p->reg2, early);
+    default: return quad_kernels_of<6>(p->reg2, early);
+  }
+}
+
 // One NCG iteration: gradient, preconditioner (+ dots), direction, and the
 // remaining line-search passes; the last pass is consumed by the next
 // iteration's gradient pass (or by the final pass).
 template <typename T, int LMAX>
 fm_status enqueue_iteration(fm_plan *p, hipStream_t s, Recorder *rec = nullptr) {
-  // FP32, 2-6 echoes, columns a multiple of 4, not a thread per voxel: the 16-byte-load passes (gradient
-  // passes of either stencil; the line-search passes have none)
-  const int quad = std::is_same<T, float>::value && p->prm.necho <= 6 && p->geo.nz % 4 == 0 && !p->few ? p->prm.necho : 0;
-  // two fours or more per thread (at five and six echoes the registers are too many)
-  const bool early = p->n >= (int64_t)8 * kMaxGrid * fm::kNT;
-  if (p->reg2) {
-    if (quad == 2)
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad2_q<2>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-    else if (quad == 3)
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad2_q<3>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-    else if (quad == 4)
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad2_q<4>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-    else if (quad == 5)
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad2_q<5>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-    else if (quad == 6)
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad2_q<6>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-    else
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad2<T, LMAX>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
-  } else if (quad == 2) {
-    if (early)
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<2, false, true>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-    else
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<2, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-  } else if (quad == 3) {
-    if (early)
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<3, false, true>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-    else
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<3, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-  } else if (quad == 4) {
-    if (early)
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<4, false, true>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-    else
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<4, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-  } else if (quad == 5) {
-    FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<5, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-  } else if (quad == 6) {
-    FM_LAUNCH(FM_K_GRAD, (fm::k_grad_q<6, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+  // FP32, 2-6 echoes, columns a multiple of 4, not a thread per voxel: the 16-byte-load passes
+  // (gradient passes of either stencil; the line-search passes have none)
+  const bool quad = std::is_same<T, float>::value && p->prm.necho <= 6 && p->geo.nz % 4 == 0 && !p->few;
+  auto launch_quad = [&](int cls, QuadKernel k) {
+    FM_LAUNCH(cls, k, dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+  };
+  if (quad) {
+    launch_quad(FM_K_GRAD, quad_kernels(p).grad);
+  } else if (p->reg2) {
+    FM_LAUNCH(FM_K_GRAD, (fm::k_grad2<T, LMAX>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
+  } else if (p->few) {
+    FM_LAUNCH(FM_K_GRAD, (fm::k_grad<T, LMAX, false, 1>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
   } else {
-    if (p->few)
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad<T, LMAX, false, 1>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
-    else
-      FM_LAUNCH(FM_K_GRAD, (fm::k_grad<T, LMAX, false, fm::kVGrad<T>>), dim3(p->sgrid), dim3(fm::kNT), s,
-                iter_args<T>(p, p->q++));
+    FM_LAUNCH(FM_K_GRAD, (fm::k_grad<T, LMAX, false, fm::kVGrad<T>>), dim3(p->sgrid), dim3(fm::kNT), s,
+              iter_args<T>(p, p->q++));
   }
   FM_LAUNCH_CHECK();
   set_parts(p, p->sgrid, 4);
@@ -693,31 +688,13 @@ fm_status enqueue_iteration(fm_plan *p, hipStream_t s, Recorder *rec = nullptr) 
   }
   set_parts(p, dir_parts, 3);
   for (int k = 1; k < p->prm.nmls; ++k) {
-    if (quad == 2) {
-      if (early)
-        FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<2, false, true>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-      else
-        FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<2, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-    } else if (quad == 3) {
-      if (early)
-        FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<3, false, true>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-      else
-        FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<3, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-    } else if (quad == 4) {
-      if (early)
-        FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<4, false, true>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-      else
-        FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<4, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-    } else if (quad == 5) {
-      FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<5, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
-    } else if (quad == 6) {
-      FM_LAUNCH(FM_K_MLS, (fm::k_mls_q<6, false>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<float>(p, p->q++));
+    if (quad) {
+      launch_quad(FM_K_MLS, quad_kernels(p).mls);
+    } else if (p->few) {
+      FM_LAUNCH(FM_K_MLS, (fm::k_mls<T, LMAX, false, 1>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
     } else {
-      if (p->few)
-        FM_LAUNCH(FM_K_MLS, (fm::k_mls<T, LMAX, false, 1>), dim3(p->sgrid), dim3(fm::kNT), s, iter_args<T>(p, p->q++));
-      else
-        FM_LAUNCH(FM_K_MLS, (fm::k_mls<T, LMAX, false, fm::kVMls<T, LMAX>>), dim3(p->sgrid), dim3(fm::kNT), s,
-                  iter_args<T>(p, p->q++));
+      FM_LAUNCH(FM_K_MLS, (fm::k_mls<T, LMAX, false, fm::kVMls<T, LMAX>>), dim3(p->sgrid), dim3(fm::kNT), s,
+                iter_args<T>(p, p->q++));
     }
     FM_LAUNCH_CHECK();
     set_parts(p, p->sgrid, 2);
@@ -817,8 +794,9 @@ fm_status validate(const fm_params *p) {
   if (p->reg_order < 0 || p->reg_order > 2) return fail(FM_ERR_ARG, "reg_order must be 1 or 2");
   if (p->reg_order == 2 && p->precond == FM_PRECOND_IC0 && p->ordering != FM_ORDER_COLOR3)
     return fail(FM_ERR_ARG, "IC(0) with second-order differences is built in three-colour order (FM_ORDER_COLOR3)");
+  // (a bound of the entry point, from when the sweeps had 32-bit offsets into a tile's planes)
   if (p->ordering == FM_ORDER_BLOCKRB && (int64_t)p->ny * p->nz * 80 >= ((int64_t)1 << 30))
-    return fail(FM_ERR_SHAPE, "block red-black order needs ny * nz * 80 below 2^30 (its per-tile views use 32-bit offsets)");
+    return fail(FM_ERR_SHAPE, "block red-black order needs ny * nz * 80 below 2^30");
   if (p->ordering == FM_ORDER_COLOR3 && (p->reg_order != 2 || p->precond != FM_PRECOND_IC0))
     return fail(FM_ERR_ARG, "three-colour order is built for IC(0) with second-order differences only");
   if (p->precond == FM_PRECOND_ICT) {
@@ -1203,13 +1181,13 @@ int stream_grid(const fm_plan *p) {
 }
 
 // Column length of the plan's arrays.  The pair and tile passes of red-black IC(0) need an even
-// one, the 16-byte-load passes (FP32, up to 6 echoes, more voxels than threads) a multiple of 4; a column is lengthened to
-// it with voxels outside the mask where that adds at most an eighth (beyond, the added bytes
-// cost more than the per-voxel passes: 10 -> 12 would add a fifth).  91x109x91, F64, 40
-// iterations: 3.97 -> 3.61 ms; drawn odd sizes 3.31 -> 2.59 and 2.91 -> 2.39 ms.  Plans that
-// qualify for the resident schedule need no more than the even length they have, orders with
-// arrays of their own (natural, block red-black, three colours, IC_t) keep the caller's, and so
-// do volumes beyond 2^26 voxels, where the memory would be missed.
+// one, the 16-byte-load passes (FP32, up to 6 echoes, more than a voxel per thread) a multiple of
+// 4; a column is lengthened to it with voxels outside the mask where that adds at most an eighth
+// (beyond, the added bytes cost more than the per-voxel passes: 10 -> 12 would add a fifth).
+// 91x109x91, F64, 40 iterations: 3.97 -> 3.61 ms.
+// Plans that qualify for the resident schedule need no more than the even length they have, orders
+// with arrays of their own (natural, block red-black, three colours, IC_t) keep the caller's, and
+// so do volumes beyond 2^26 voxels, where the memory would be missed.
 int32_t padded_columns(const fm_plan *p) {
   const fm_params &q = p->prm;
   const bool rb = q.precond == FM_PRECOND_IC0 && q.ordering == FM_ORDER_REDBLACK;

@@ -380,9 +380,10 @@ __global__ __launch_bounds__(64) void k_ict_fwd_wave(IctSweep w, int32_t *status
       const bool good = diag > 0.0, fin = fabs(diag) < __builtin_inf();
       bad5 |= !good && fin;
       bad6 |= !good && !fin;
-      // L_jj = sqrt(diag) and 1 / L_jj: the steps of a square root without its
-      // scaling, which a normal diag does not need (the same value), and the
-      // reciprocal from the half of 1 / sqrt that they carry
+      // L_jj = sqrt(diag) and 1 / L_jj: Goldschmidt's coupled iteration for a square
+      // root and half its reciprocal from the hardware's estimate (l ~ sqrt, r ~ 1 / (2 sqrt)),
+      // two corrections of l by its exact residual, and two Newton steps for the
+      // reciprocal of l; no scaling, which a normal diag does not need
       const double q = __builtin_amdgcn_rsq(diag);
       double l = diag * q, r = 0.5 * q;
       double e = fma(-r, l, 0.5);

@@ -215,8 +215,8 @@ __global__ __launch_bounds__(kNT) void k_nat_pack(IterArgs<T> a, Wavefront w, co
   using U = typename Bits<T>::U;
   if (blockIdx.x == 0) {  // the gradient pass's sums: no other block needs them
     const State st = take_state<kNT, 4>(a.sin, a.pin, a.nparts_in, a.nvals_in, a.beta, a.trace, a.status);
-  put_state(st, a.sout, PK_NONE, 0);
-      if (w.ff && threadIdx.x < 2) w.ticket[threadIdx.x] = 0u;
+    put_state(st, a.sout, PK_NONE, 0);
+    if (w.ff && threadIdx.x < 2) w.ticket[threadIdx.x] = 0u;
   }
   // one wavefront per 8 rows and column a: lane (s, b) writes the record of lane
   // (a, b) in row 8 i + s, so its loads run along z and its stores along b
@@ -357,8 +357,9 @@ struct FwdLane {
     else
       xx = (double)(fx ? rec_t(fxr, T()) : xxl);
     FM_STAGE;
-    // 1 / piv by the Newton steps of a division, which give the same value
-    // for a normal pivot, without its scaling and special cases
+    // 1 / piv by Newton's iteration q <- q + q (1 - piv q) from the hardware's estimate, with
+    // the last residual exact (Markstein 1990, as the quotients of fm_ict_tile.hpp): the value
+    // of a division for a normal pivot, without its scaling and special cases
     double e = fma(-piv, q, 1.0);
     const double x2 = x1 + xx;
     FM_STAGE;
