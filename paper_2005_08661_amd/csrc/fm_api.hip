@@ -1163,14 +1163,15 @@ void plan_geometry(fm_plan *p, int32_t nz) {
 // - FP64 otherwise (the passes of the diagonal with few echoes are short, those of second order
 //   keep their own voxels per thread): a workgroup per compute unit.  62 208 voxels, diagonal 575 ->
 //   525 us, second order 648 -> 612; 92 400 voxels, 603 -> 621 and 682 -> 727.
-bool few_voxels(const fm_params &q) {
+// The voxels counted are those of the plan's arrays.
+bool few_voxels(const fm_params &q, int64_t n) {
   const bool order2 = q.reg_order == 2;
   int64_t most = 65536;
   if (q.precision == FM_PREC_MIX)
     most = 131072;
   else if (!order2 && (q.precond == FM_PRECOND_IC0 || q.precond == FM_PRECOND_ICT || q.necho > 4))
     most = 196608;
-  return (int64_t)q.nx * q.ny * q.nz <= most &&
+  return n <= most &&
          !(order2 && q.precision == FM_PREC_MIX && q.necho <= 6 && q.nz % 4 == 0);
 }
 
@@ -1183,8 +1184,12 @@ int stream_grid(const fm_plan *p) {
 // Column length of the plan's arrays.  The pair and tile passes of red-black IC(0) need an even
 // one, the 16-byte-load passes (FP32, up to 6 echoes, more than a voxel per thread) a multiple of
 // 4; a column is lengthened to it with voxels outside the mask where that adds at most an eighth
-// (beyond, the added bytes cost more than the per-voxel passes: 10 -> 12 would add a fifth).
-// 91x109x91, F64, 40 iterations: 3.97 -> 3.61 ms.
+// (beyond, the added bytes cost more than the per-voxel passes: 10 -> 12 would add a fifth), and
+// by at most a fifteenth where the gain is smaller: FP64 volumes with a voxel per thread (above
+// 65536 voxels), and the diagonal's passes with few echoes, which are bound by bytes, above 2^20.
+// Unpadded -> padded, 40 iterations: 91x109x91 F64 3.84 -> 3.39 ms, 75x60x33 MIX 1.41 -> 1.35,
+// 256x250x121 MIX 15.2 -> 10.5, 90x85x18 MIX with six echoes 2.00 -> 1.81; 20 iterations, not
+// padded for it: 105x105x9 F64 0.71 -> 0.74, 244x245x25 MIX diagonal 1.51 -> 1.66.
 // Plans that qualify for the resident schedule need no more than the even length they have, orders
 // with arrays of their own (natural, block red-black, three colours, IC_t) keep the caller's, and
 // so do volumes beyond 2^26 voxels, where the memory would be missed.
@@ -1192,11 +1197,26 @@ int32_t padded_columns(const fm_plan *p) {
   const fm_params &q = p->prm;
   const bool rb = q.precond == FM_PRECOND_IC0 && q.ordering == FM_ORDER_REDBLACK;
   const bool none = q.precond == FM_PRECOND_DIAG || q.precond == FM_PRECOND_NONE;
-  if (p->reg2 || p->res_ok || !(rb || none) || p->n > ((int64_t)1 << 26)) return q.nz;
+  const int64_t n = (int64_t)q.nx * q.ny * q.nz;
+  if (p->reg2 || p->res_ok || !(rb || none) || n > ((int64_t)1 << 26)) return q.nz;
   const int32_t up4 = (q.nz + 3) / 4 * 4, up2 = (q.nz + 1) / 2 * 2;
-  if (p->mix && q.necho <= 6 && !p->few && 8 * (up4 - q.nz) <= q.nz) return up4;
-  if (rb && 8 * (up2 - q.nz) <= q.nz) return up2;
+  const int at_most4 = none && q.necho <= 4 && n > ((int64_t)1 << 20) ? 15 : 8;
+  const int at_most2 = !p->mix && p->few && n > 65536 ? 15 : 8;
+  if (p->mix && q.necho <= 6 && !p->few && at_most4 * (up4 - q.nz) <= q.nz) return up4;
+  if (rb && at_most2 * (up2 - q.nz) <= q.nz) return up2;
   return q.nz;
+}
+
+// Columns and threads of a plan whose precision, regulariser and resident schedule are set:
+// a volume that its padding takes past the line of a thread per voxel is not one of few voxels.
+void plan_columns(fm_plan *p) {
+  plan_geometry(p, p->prm.nz);
+  p->few = few_voxels(p->prm, p->n);
+  plan_geometry(p, padded_columns(p));
+  if (p->few && !few_voxels(p->prm, p->n)) {
+    p->few = false;
+    plan_geometry(p, padded_columns(p));
+  }
 }
 
 fm_status run_graph(fm_plan *p, int niter, hipStream_t s);
@@ -1572,7 +1592,6 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
   p->mix = prm->precision == FM_PREC_MIX;
   p->tsize = p->mix ? sizeof(float) : sizeof(double);
   p->reg2 = prm->reg_order == 2;
-  p->few = few_voxels(*prm);
   plan_geometry(p, prm->nz);
   p->cm = p->reg2 && prm->precond == FM_PRECOND_IC0;
   if (p->cm) {
@@ -1588,7 +1607,7 @@ fm_status fm_plan_create(const fm_params *prm, fm_plan **out) {
     return fail(FM_ERR_HIP, "hipGetDevice failed");
   }
   p->res_ok = plan_resident(p);
-  plan_geometry(p, padded_columns(p));  // (at most 9/8 of 2^26 voxels: no index bound to check again)
+  plan_columns(p);  // (at most 9/8 of 2^26 voxels: no index bound to check again)
   p->lmax = prm->necho <= 4 ? 4 : (prm->necho <= 8 ? 8 : 16);
   const int64_t blocks = (p->n + kBlock - 1) / kBlock;
   p->grid = (int)(blocks < kMaxGrid ? blocks : kMaxGrid);

@@ -1,7 +1,9 @@
-"""The lines of the thread-per-voxel rule in FP64 (65 536 voxels for second order and for the diagonal preconditioner
+"""Lines of the rules that choose passes by size.  The thread-per-voxel rule in FP64 (65 536 voxels for second order and for the diagonal preconditioner
 with up to 4 echoes, 196 608 for the rest): the last volume below and the first above each, on the streaming schedule
 against the oracle (1e-6 Hz; where its factor breaks down, the same status), and past the line no more time a voxel
-than a larger volume takes (the second-order diagonal, where a thread per voxel cost a fifth at 245 760 voxels)."""
+than a larger volume takes (the second-order diagonal, where a thread per voxel cost a fifth at 245 760 voxels).  And the columns that are padded:
+in FP64 with a thread per voxel from 65 536 voxels on, and for the diagonal in FP32 above 2^20, only by a fifteenth; a
+volume that its padding takes past the line has several voxels a thread (FP32 bar: 0.05 Hz RMS)."""
 import time
 
 import numpy as np
@@ -44,6 +46,26 @@ def test_either_side_matches_oracle(kind, necho, shape):
         plan.status()
     assert np.all(f[vol.mask == 0] == 0)
     assert np.abs(f - ref["f"]).max() < 1e-6
+
+
+# F64: 9 and 13 not padded, 15 -> 16; below 65 536 voxels 9 -> 10; past 196 608 by their padding 145x145x9, 105x106x17
+# and 88x88x25.  MIX diagonal: 25 not padded above 2^20 voxels, 30 -> 32; below, 25 -> 28
+COLUMNS = [("redblack", "f64", (105, 105, 9)), ("redblack", "f64", (85, 84, 13)), ("redblack", "f64", (81, 82, 15)),
+           ("redblack", "f64", (85, 85, 9)), ("redblack", "f64", (145, 145, 9)), ("redblack", "f64", (105, 106, 17)),
+           ("redblack", "f64", (88, 88, 25)), ("diag", "mix", (210, 210, 25)), ("diag", "mix", (190, 190, 30)),
+           ("diag", "mix", (100, 99, 25))]
+
+
+@pytest.mark.parametrize("kind,prec,shape", COLUMNS, ids=lambda v: str(v))
+def test_columns_either_side_match_oracle(kind, prec, shape):
+    vol, kw = setting(kind, 3, shape, 3)
+    y, s, m = fmap.to_device(vol, "cuda:0")
+    with fmap.Plan(fmap.params_for(vol, precision=fmap.F64 if prec == "f64" else fmap.MIX, **kw)) as plan:
+        f = plan.solve(y, s, m).cpu().numpy()
+        plan.status()
+    d = np.abs(f - O.run_volume(vol, **kw)["f"])[vol.mask != 0]
+    assert np.all(f[vol.mask == 0] == 0)
+    assert d.max() < 1e-6 if prec == "f64" else np.sqrt(np.mean(d ** 2)) < 0.05
 
 
 def test_no_more_time_a_voxel_than_a_larger_volume():
