@@ -452,6 +452,7 @@ fm_status enqueue_block(fm_plan *p, const fm::IterArgs<T> &ain, const fm::IterAr
 template <typename T, bool BLOCK>
 fm_status enqueue_ic_levels(fm_plan *p, const fm::IterArgs<T> &ia, const T *gsrc, hipStream_t s, Recorder *rec) {
   const fm::Geo &g = p->geo;
+  if (!ia.X) return fail(FM_ERR_ALLOC, "no memory for the level sweeps (the packed rows were given back)");
   const int per_x = BLOCK ? g.ny : std::min(g.ny, g.nz), nlev = BLOCK ? g.nz + 2 * (fm::kTile - 1) : g.nx + g.ny + g.nz - 2;
   fm::LevelArgs<T> a{g,     ia.beta, ia.code, ia.D, gsrc ? gsrc : ((ia.par & 1) ? ia.G[1] : ia.G[0]),
                      ia.X,  ia.P,    ia.ipiv, ia.status, per_x};
