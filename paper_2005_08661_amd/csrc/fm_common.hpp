@@ -487,7 +487,7 @@ __device__ __forceinline__ State take_state(const State *__restrict__ sin, const
 // voxel loop it cost the passes a third of their waves (k_mls_q<3> 85 -> 54 VGPRs,
 // k_mls_q<6> 152 -> 118, F64 k_mls 169 -> 107).  192x192x64 water-fat 17.5 -> 15.8 ms,
 // 91x109x91 F64 3.61 -> 3.36 ms, 16 volumes 62.3 -> 60.9 ms, second order 8.9 -> 8.6 ms,
-// the same bits.
+// the same bits.  (Some FP64 second-order passes are faster with it at their end.)
 __device__ __forceinline__ void put_state(State s, State *__restrict__ sout, int kind, int nparts,
                                           bool leader = blockIdx.x == 0) {
   if (leader && threadIdx.x == 0) {

@@ -33,8 +33,8 @@
 // An infinite L_kk stands as the largest finite number with the reciprocal 0, by
 // which every quotient is 0; y and p take an infinite numerator through v_div_fixup.
 //
-// Measured at 128x128x64 (MIX, level 1): forward 3.0 ms -> 500 us, backward 2.8 ms
-// -> 323 us a sweep, k_ict_pack 20 us and k_ict_unpack 15 us on top.  A step takes
+// Measured at 128x128x64 (MIX, level 1): forward 3.0 ms -> 497 us, backward 2.8 ms
+// -> 330 us a sweep, k_ict_pack 19 us and k_ict_unpack 14 us on top.  A step takes
 // 0.48 us forward and 0.30 us backward, of which the issue of its nine 16-byte
 // stores is a good part: stored while the next step's LDS reads are under way they
 // cost 613 -> 500 us, and the face values stored ahead of that instead (a shorter

@@ -32,12 +32,11 @@
 //   group before; the records it takes per step (one load, two stores) stay
 //   below the 64 memory operations a wave may have in flight.
 //
-// Measured at 128x128x64 (MIX), per launch: forward 598 -> 104 us, backward
+// Measured at 128x128x64 (MIX), per launch: forward 598 -> 105 us, backward
 // 550 -> 92 us (89 us without the select of p, which lengthens the chain), k_nat_pack
 // 12 and k_nat_unpack 13 us on top; a step takes 0.105 and 0.06 us (0.7 us before), a
-// hop about 3 us (21 us before).  Groups of 4
-// steps shorten a hop and lengthen every step (a group's loads take 1.7 us to
-// arrive): 117 against 109 us forward.
+// hop about 3 us (21 us before).  Groups of 4 steps shorten a hop and lengthen every
+// step (a group's loads take 1.7 us to arrive): 117 against 109 us forward.
 //
 // Progress is deadlock-free: a wave takes a ticket from an atomic counter and
 // processes the tile of that rank in anti-diagonal order, so it only waits on
@@ -612,8 +611,8 @@ __global__ __launch_bounds__(64) void k_ic_bwd_wave(Wavefront w, double beta, in
 // across a tile face (colour 0, factored by the previous launch); its later
 // neighbours are the in-tile +x, +y, +z ones and, in a colour-0 tile, every
 // neighbour across a face.  Forward: colour 0, then colour 1; backward:
-// colour 1, then colour 0.  (128x128x64 MIX, per launch: 11.3 and 16.7 us
-// forward, 7.9 and 8.7 us backward; 27.7 and 30.1 us with masks, address
+// colour 1, then colour 0.  (128x128x64 MIX, per launch: 11.3 and 16.8 us
+// forward, 8.4 and 8.9 us backward; 27.7 and 30.1 us with masks, address
 // arithmetic and dot products in the step.)  A lane reads the column across its x face and the
 // one across its y face from that tile's packed rows (7 steps ahead for a lower
 // face, 7 behind for an upper one); a lane without one reads the tile that holds 0.

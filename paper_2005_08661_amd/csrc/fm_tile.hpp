@@ -20,9 +20,9 @@
 // makes every later wait a full one.  The LDS copy alternates between two
 // buffers, so one barrier per plane suffices.  One pair slot per thread and
 // two planes ahead keep FP32 at 4 waves per SIMD, all that the partial sums'
-// 1024 workgroups fill.  256x256x128 MIX: black 48.6 -> 38.6 us, red and
-// direction 49.8 -> 38.2 us (4.5 and 6.4 TB/s of 20.8 and 29 B a voxel); with
-// waits for the newest load the red pass was at 57 us.
+// 1024 workgroups fill.  256x256x128 MIX: black 48.6 -> 40 us, red and
+// direction 49.8 -> 39 us (20.8 and 29.1 B a voxel across the L2 by the traffic
+// counters, 4.4 and 6.2 TB/s); with waits for the newest load the red pass was at 57 us.
 #pragma once
 
 #include "fm_stream.hpp"
